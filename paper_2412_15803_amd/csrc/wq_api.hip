@@ -273,7 +273,7 @@ wq_status decode_grouped(const char* fn, const wq_linear* lin, int64_t count, in
     for (size_t i = 0; i < groups.size(); ++i) {
         if (!groups[i].grouped) continue;
         if (m == 1) gplans[i] = wq::plan::plan_group(lin, groups[i], ws->shape.blocks4, ws->shape.blocks8, pb);
-        else if (matrix) bplans[i] = wq::plan::plan_batch_group(lin, groups[i], pb);
+        else if (matrix) bplans[i] = wq::plan::plan_batch_group(lin, groups[i], m, pb);
         else bplans[i] = wq::plan::plan_vector_group(lin, groups[i], target, pb);
     }
     if (pb.overflow) return fail(WQ_ERR_INVALID_ARG, "%s: internal plan bound exceeded", fn);
@@ -391,13 +391,12 @@ wq_status wq_decode_linears(const wq_linear* linears, int64_t count, int64_t M, 
     (void)hipGetLastError();
     const hipStream_t s = static_cast<hipStream_t>(stream);
     if (M <= wq::kMaxSmallBatchM) return decode_grouped(fn, linears, count, M, s);
-    // Larger batches: one launch per linear, in stream order.
-    for (int64_t i = 0; i < count; ++i) {
-        const wq_linear& l = linears[i];
-        const wq_status r = hip_status(fn, wq::launch_gemv(l.packed_w, l.scales, l.x, l.y, l.N, l.K, M, s));
-        if (r != WQ_OK) return r;
-    }
-    return WQ_OK;
+    // Larger batches: the launches carry their descriptors, no plan.
+    std::vector<Group> groups;
+    wq::plan::SpanSet reads, writes;
+    wq::plan::split_groups(linears, (int)count, M, reads, writes, [&](const Group& g) { groups.push_back(g); });
+    return hip_status(fn, wq::plan::launch_groups(linears, groups.data(), (int)groups.size(), nullptr, nullptr, nullptr,
+                                                  M, true, s));
 }
 
 }  // extern "C"

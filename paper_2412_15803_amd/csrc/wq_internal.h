@@ -33,14 +33,9 @@ hipError_t launch_gemv(const uint32_t* packed, const uint16_t* scales,
 // against 1624 us), the vector kernel at M = 2 (395 against 479 us).
 constexpr int kMatrixCoreMinM = 3;
 
-// Largest batch of the small-batch kernels; larger ones (prompts) run the
-// tiled prefill GEMM.
+// Largest batch of the planned decode steps (and of the vector kernel);
+// larger ones (prompts) keep no plan.
 constexpr int kMaxSmallBatchM = 64;
-
-// y[M][N] for M > kMaxSmallBatchM: 128 x 128 tiles on the matrix cores, for
-// the shapes prefill_fits (wq_limits.h) accepts.
-hipError_t launch_prefill(const uint32_t* packed, const uint16_t* scales, const uint16_t* x, uint16_t* y,
-                          int64_t n, int64_t k, int64_t m, hipStream_t stream);
 
 // Whether a small batch of m rows (2 <= m <= kMaxSmallBatchM) runs on the
 // matrix cores: from kMatrixCoreMinM rows on.  Tuning overrides, read at
@@ -49,9 +44,14 @@ hipError_t launch_prefill(const uint32_t* packed, const uint16_t* scales, const 
 // threshold to n.
 bool use_matrix_cores(int64_t m);
 
-// y[M][N] for 2 <= M on the matrix cores, 16 batch rows per launch.
-hipError_t launch_gemm_mfma(const uint32_t* packed, const uint16_t* scales, const uint16_t* x, uint16_t* y,
-                            int64_t n, int64_t k, int64_t m, hipStream_t stream);
+// y[M][N] on the matrix cores, any M (wq_gemm.hip), for the shapes gemm_fits
+// (wq_limits.h) accepts.
+hipError_t launch_gemm(const uint32_t* packed, const uint16_t* scales, const uint16_t* x, uint16_t* y,
+                       int64_t n, int64_t k, int64_t m, hipStream_t stream);
+
+// Independent linears at M > kMaxSmallBatchM, as few launches as their
+// arguments allow; every one fits gemm_fits.
+hipError_t launch_gemm_list(const wq_linear* lin, int count, int64_t m, hipStream_t stream);
 
 // One linear of a grouped launch as the kernel sees it (built on the host,
 // uploaded once per distinct descriptor list).
@@ -104,16 +104,14 @@ struct DecodePlan {
     int32_t nclasses;
 };
 
-// Small-batch decode step: independent linears in one launch of the matrix-core
-// kernel.  Entry i owns blocks [first_step, first_step + steps) of the grid,
-// each block grouped_mfma_tiles() tiles of 16 rows, waves_per_block <=
-// grouped_mfma_max_waves();
-// batch rows [m0, m0 + m), m <= 16.
-int grouped_mfma_tiles();
-// Most waves a block of the matrix-core kernels has (LDS per wave).
-int grouped_mfma_max_waves();
-hipError_t launch_grouped_mfma(const DecodeEntry* entries, int count, int64_t blocks, int waves_per_block,
-                               int64_t m0, int m, hipStream_t stream);
+// Small-batch decode step: independent linears in one launch of the
+// matrix-core kernel.  The block shape is picked for the whole list; entry i
+// owns blocks [first_step, first_step + steps) of the grid, ceil(n / rows) x
+// blocks_m of them.
+int gemm_plan_config(const wq_linear* lin, int count, int64_t m);
+int gemm_plan_rows(int config);
+int64_t gemm_plan_blocks_m(int config, int64_t m);
+hipError_t launch_gemm_plan(int config, const DecodeEntry* entries, int count, int64_t blocks, int m, hipStream_t stream);
 
 // Small-batch decode step below kMatrixCoreMinM rows (or any small batch when
 // forced): independent linears in

@@ -624,10 +624,9 @@ hipError_t launch_gemv(const uint32_t* packed, const uint16_t* scales, const uin
 #undef WQ_M1_CASE
     }
     if (m >= 2 && m <= kMaxSmallBatchM && fits_rsrc(n, ng)) {
-        // Matrix cores from 8 batch rows on (measured faster than the vector
-        // kernel there); below that, or when asked to, the vector kernel in
-        // passes of up to 8 rows.
-        if (use_matrix_cores(m)) return launch_gemm_mfma(packed, scales, x, y, n, k, m, stream);
+        // Matrix cores from kMatrixCoreMinM batch rows on; below that, or
+        // when asked to, the vector kernel in passes of up to 8 rows.
+        if (use_matrix_cores(m) && gemm_fits(n, k, m)) return launch_gemm(packed, scales, x, y, n, k, m, stream);
         for (int64_t m0 = 0; m0 < m; m0 += 8) {
             const int mc = (int)min((int64_t)8, m - m0);
             const uint16_t* xc = x + m0 * k;
@@ -640,7 +639,7 @@ hipError_t launch_gemv(const uint32_t* packed, const uint16_t* scales, const uin
         return hipSuccess;
     }
     // Prompt-sized batches: the tiled matrix-core GEMM.
-    if (m > kMaxSmallBatchM && prefill_fits(n, k, m)) return launch_prefill(packed, scales, x, y, n, k, m, stream);
+    if (m > kMaxSmallBatchM && prefill_fits(n, k, m)) return launch_gemm(packed, scales, x, y, n, k, m, stream);
     constexpr int MC = 4;
     const int64_t mchunks = (m + MC - 1) / MC;
     const int64_t waves = n * mchunks;

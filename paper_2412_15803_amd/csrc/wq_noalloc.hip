@@ -136,32 +136,27 @@ extern "C" wq_status wq_decode_linears_noalloc(const wq_linear* linears, int64_t
     if (st != WQ_OK) return st;
     (void)hipGetLastError();
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    if (M > kMaxSmallBatchM) {
-        // Prompt-sized batches: one launch per linear, no plan.
-        for (int64_t i = 0; i < count; ++i) {
-            const wq_linear& l = linears[i];
-            if ((st = hip_error(fn, launch_gemv(l.packed_w, l.scales, l.x, l.y, l.N, l.K, M, s))) != WQ_OK) return st;
-        }
-        return WQ_OK;
+    int ngroups = 0;
+    {
+        plan::SpanList reads(g_reads, kMaxLinears), writes(g_writes, kMaxLinears);
+        plan::split_groups(linears, (int)count, M, reads, writes, [&](const Group& g) { g_groups[ngroups++] = g; });
     }
+    // Prompt-sized batches: the launches carry their descriptors, no plan.
+    if (M > kMaxSmallBatchM)
+        return hip_error(fn, plan::launch_groups(linears, g_groups, ngroups, nullptr, nullptr, nullptr, M, true, s));
     int device = 0;
     hipError_t e = hipGetDevice(&device);
     if (e != hipSuccess) return hip_error(fn, e);
     DeviceState* ds = nullptr;
     if ((st = device_state(fn, device, ds)) != WQ_OK) return st;
 
-    int ngroups = 0;
-    {
-        plan::SpanList reads(g_reads, kMaxLinears), writes(g_writes, kMaxLinears);
-        plan::split_groups(linears, (int)count, M, reads, writes, [&](const Group& g) { g_groups[ngroups++] = g; });
-    }
     const bool matrix = use_matrix_cores(M);
     const int64_t target = ds->shape.mb_waves[M <= 2 ? 0 : M <= 4 ? 1 : 2];
     PlanBuf pb{g_plan, kScratchBytes, 0, false};
     for (int i = 0; i < ngroups; ++i) {
         if (!g_groups[i].grouped) continue;
         if (M == 1) g_gplans[i] = plan::plan_group(linears, g_groups[i], ds->shape.blocks4, ds->shape.blocks8, pb);
-        else if (matrix) g_bplans[i] = plan::plan_batch_group(linears, g_groups[i], pb);
+        else if (matrix) g_bplans[i] = plan::plan_batch_group(linears, g_groups[i], M, pb);
         else g_bplans[i] = plan::plan_vector_group(linears, g_groups[i], target, pb);
     }
     if (pb.overflow)

@@ -96,8 +96,9 @@ constexpr int64_t kGroupMaxRows = int64_t(1) << 30;
 // output of, or writes the input or output of, another linear of the same
 // group.  Groups run in stream order, so this reproduces running the linears
 // one after another.  Linears the grouped kernels cannot take (K > 16384 at
-// M = 1, or codes of 4 GiB or more) form groups of their own, and a group
-// closes before its rows would pass kGroupMaxRows.  Calls emit(Group) in
+// M = 1, codes of 4 GiB or more, or x rows beyond gemm_fits or, for prompts,
+// prefill_fits) form groups of their own, and a group closes before its rows
+// would pass kGroupMaxRows.  Calls emit(Group) in
 // order; `reads` and `writes` are empty dependency sets.
 template <class Deps, class Emit>
 void split_groups(const wq_linear* lin, int count, int64_t m, Deps& reads, Deps& writes, Emit emit) {
@@ -106,7 +107,8 @@ void split_groups(const wq_linear* lin, int count, int64_t m, Deps& reads, Deps&
     for (int i = 0; i < count; ++i) {
         const wq_linear& l = lin[i];
         const bool too_long = m == 1 && l.K / 32 > 64 * kDecodeMaxGpl;
-        if (too_long || !fits_rsrc(l.N, l.K / 32)) {
+        const bool too_wide = m > 2 && !(m > kMaxSmallBatchM ? prefill_fits(l.N, l.K, m) : gemm_fits(l.N, l.K, m));
+        if (too_long || too_wide || !fits_rsrc(l.N, l.K / 32)) {
             if (i > begin) emit(Group{begin, i, true});
             emit(Group{i, i + 1, false});
             reads.clear();
@@ -161,7 +163,7 @@ struct BatchPlan {
     size_t off_entries;
     int count;
     int64_t blocks;
-    int waves_per_block;
+    int config;  // block shape (matrix cores)
 };
 
 // Append the batch-1 plan of linears [g.begin, g.end); `capacity4` and
@@ -169,8 +171,8 @@ struct BatchPlan {
 // wide grouped kernels.
 GroupPlan plan_group(const wq_linear* lin, const Group& g, int capacity4, int capacity8, PlanBuf& out);
 
-// Append the matrix-core (M >= 3) plan of a group.
-BatchPlan plan_batch_group(const wq_linear* lin, const Group& g, PlanBuf& out);
+// Append the matrix-core (M >= 3) plan of a group at m rows.
+BatchPlan plan_batch_group(const wq_linear* lin, const Group& g, int64_t m, PlanBuf& out);
 
 // Append the vector small-batch (M < 8) plan of a group, `target` waves.
 BatchPlan plan_vector_group(const wq_linear* lin, const Group& g, int64_t target, PlanBuf& out);

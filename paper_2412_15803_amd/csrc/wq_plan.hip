@@ -143,16 +143,11 @@ GroupPlan plan_group(const wq_linear* lin, const Group& g, int capacity4, int ca
     return gp;
 }
 
-#ifndef WQ_MFMA_WAVE_STEPS
-#define WQ_MFMA_WAVE_STEPS 32
-#endif
-constexpr int64_t kMfmaWaveSteps = WQ_MFMA_WAVE_STEPS;
-
-BatchPlan plan_batch_group(const wq_linear* lin, const Group& g, PlanBuf& out) {
+BatchPlan plan_batch_group(const wq_linear* lin, const Group& g, int64_t m, PlanBuf& out) {
     const int count = g.end - g.begin;
-    const int rows_per_block = 16 * grouped_mfma_tiles();
     BatchPlan bp{};
     bp.count = count;
+    bp.config = gemm_plan_config(lin + g.begin, count, m);
     bp.off_entries = align16(out.size);
     const size_t end = align16(bp.off_entries + sizeof(DecodeEntry) * count);
     if (out.overflow || end > out.cap) {
@@ -161,21 +156,18 @@ BatchPlan plan_batch_group(const wq_linear* lin, const Group& g, PlanBuf& out) {
     }
     std::memset(out.data + out.size, 0, end - out.size);
     DecodeEntry* ents = reinterpret_cast<DecodeEntry*>(out.data + bp.off_entries);
-    int64_t blocks = 0, max_steps = 1;
+    const int rows = gemm_plan_rows(bp.config);
+    const int64_t blocks_m = gemm_plan_blocks_m(bp.config, m);
+    int64_t blocks = 0;
     for (int i = 0; i < count; ++i) {
         const wq_linear& l = lin[g.begin + i];
         DecodeEntry& e = ents[i];
         fill_entry(e, l);
         e.first_step = blocks;
-        e.steps = (l.N + rows_per_block - 1) / rows_per_block;
+        e.steps = (l.N + rows - 1) / rows * blocks_m;
         blocks += e.steps;
-        max_steps = std::max<int64_t>(max_steps, (e.ng + 3) / 4);
     }
     bp.blocks = blocks;
-    // About 32 steps of the longest row per wave (measured on the 3B- and
-    // 8B-class steps: fewer, longer waves keep more blocks resident per CU),
-    // at most 4 (each wave's scale-window slots take 16 KiB of LDS).
-    bp.waves_per_block = (int)std::min<int64_t>(grouped_mfma_max_waves(), (max_steps + kMfmaWaveSteps - 1) / kMfmaWaveSteps);
     out.size = end;
     return bp;
 }
@@ -188,7 +180,6 @@ BatchPlan plan_vector_group(const wq_linear* lin, const Group& g, int64_t target
     const int count = g.end - g.begin;
     BatchPlan bp{};
     bp.count = count;
-    bp.waves_per_block = 0;
     bp.off_entries = align16(out.size);
     const size_t end = align16(bp.off_entries + sizeof(DecodeEntry) * count);
     if (out.overflow || end > out.cap) {
@@ -245,7 +236,9 @@ hipError_t launch_groups(const wq_linear* lin, const Group* groups, int ngroups,
     for (int i = 0; i < ngroups; ++i) {
         const Group& g = groups[i];
         hipError_t e = hipSuccess;
-        if (!g.grouped) {
+        if (m > kMaxSmallBatchM && g.grouped) {
+            e = launch_gemm_list(lin + g.begin, g.end - g.begin, m, stream);
+        } else if (!g.grouped) {
             for (int j = g.begin; j < g.end && e == hipSuccess; ++j)
                 e = launch_gemv(lin[j].packed_w, lin[j].scales, lin[j].x, lin[j].y, lin[j].N, lin[j].K, m, stream);
         } else if (m == 1) {
@@ -260,11 +253,11 @@ hipError_t launch_groups(const wq_linear* lin, const Group* groups, int ngroups,
         } else {
             const BatchPlan& bp = bplans[i];
             const DecodeEntry* ents = reinterpret_cast<const DecodeEntry*>(d_plan + bp.off_entries);
-            const int64_t chunk = matrix ? 16 : 8;
-            for (int64_t m0 = 0; m0 < m && e == hipSuccess; m0 += chunk) {
-                const int mc = (int)std::min<int64_t>(chunk, m - m0);
-                e = matrix ? launch_grouped_mfma(ents, bp.count, bp.blocks, bp.waves_per_block, m0, mc, stream)
-                           : launch_grouped_mb(ents, bp.count, bp.blocks, m0, mc, stream);
+            if (matrix) {
+                e = launch_gemm_plan(bp.config, ents, bp.count, bp.blocks, (int)m, stream);
+            } else {
+                for (int64_t m0 = 0; m0 < m && e == hipSuccess; m0 += 8)
+                    e = launch_grouped_mb(ents, bp.count, bp.blocks, m0, (int)std::min<int64_t>(8, m - m0), stream);
             }
         }
         if (e != hipSuccess) return e;

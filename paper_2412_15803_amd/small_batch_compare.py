@@ -84,7 +84,7 @@ def summarise(trace_dir, out):
     for f in glob.glob(os.path.join(trace_dir, "**", "*kernel_trace.csv"), recursive=True):
         with open(f, newline="") as fh:
             rows.extend(csv.DictReader(fh))
-    launches = [r for r in rows if "gemv_mb_kernel" in r["Kernel_Name"] or "gemm_mfma_kernel" in r["Kernel_Name"]]
+    launches = [r for r in rows if "gemv_mb_kernel" in r["Kernel_Name"] or "gemm_kernel" in r["Kernel_Name"]]
     launches.sort(key=lambda r: int(r["Start_Timestamp"]))
     lines = ["# Small batches: vector-ALU kernel against matrix-core kernel", "",
              "Commands (from /tmp with TMPDIR=/tmp and PYTHONPATH=<repo>, one MI355X):", "", "```",
@@ -109,7 +109,7 @@ def summarise(trace_dir, out):
         per = sum(durs) / CALLS
         kname = timed[0]["Kernel_Name"].split("(")[0].split("::")[-1]
         if "<" not in kname:
-            kname = "gemv_mb_kernel" if "gemv_mb_kernel" in timed[0]["Kernel_Name"] else "gemm_mfma_kernel"
+            kname = "gemv_mb_kernel" if "gemv_mb_kernel" in timed[0]["Kernel_Name"] else "gemm_kernel"
         ideal = n * k // 2 + n * (k // 32) * 2 + 2 * m * k + 2 * m * n
         lines.append(f"| {n}x{k} | {m} | {path} | `{kname}` | {per_call} | {per:.2f} | {ideal / (per * 1e3):.1f} |")
     lines.append("")

@@ -1,0 +1,105 @@
+"""GPU parity of the matrix-core GEMM's block shapes (wq_gemm.hip): every
+compiled shape (forced with WQ_GEMM_CONFIG) at sizes that leave remainders in
+M, N and K, with scales on both sides of the short dequantization's limit and
+scale arrays that start in the middle of a dword.
+
+Inputs are integer-exact: x in {-4..4} and scales 2^e, e in [-10, -2], so every
+product is a multiple of 2^-10 and every sum of K = 1056 of them at most
+4 * 8 * 2^-2 * 1056 < 2^14; all partial sums are exact in fp32 and the result
+is unique up to its one fp16 rounding, so the comparison is bit for bit.
+"""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import announce, gpu_gemv, to_dev, to_host
+from paper_2412_15803_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CONFIGS = 24  # rows of WQ_GEMM_CONFIGS; the first 5 take 16 rows of x per block
+ONE_TILE = 5
+
+
+def _case(m, n, k, seed, shift=0, lo=-10, hi=-2):
+    import torch
+
+    packed = wl.random_words_host(seed, n, k)
+    scales = wl.pow2_scales_host(seed + 1, n, k, lo, hi)
+    x = wl.small_int_x_host(seed + 2, m, k)
+    ng = k // 32
+    buf = torch.zeros(n * ng + shift, dtype=torch.int16, device="cuda:0")
+    buf[shift:] = to_dev(scales).reshape(-1)
+    return packed, scales, x, buf[shift:].view(n, ng)
+
+
+def _check(m, n, k, seed, shift=0):
+    packed, scales, x, sd = _case(m, n, k, seed, shift)
+    y = to_host(gpu_gemv(to_dev(packed), sd, to_dev(x)), np.uint16)
+    ref = oracle.gemv(packed, scales, x, n, k).view(np.uint16)
+    bad = np.argwhere(y != ref)
+    assert bad.size == 0, f"{len(bad)} mismatches, first {bad[:5].tolist()}"
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("config", range(CONFIGS))
+def test_block_shape_exact(config, shift, monkeypatch):
+    """One block past a whole number of them in N, a ragged M over two or
+    more blocks of rows, and K = 4 whole stages and one group."""
+    monkeypatch.setenv("WQ_GEMM_CONFIG", str(config))
+    m = 19 if config < ONE_TILE else 131
+    announce(f"gemm config {config} M={m} N=530 K=1056 scale shift {shift}")
+    _check(m, 530, 1056, 100 * config + shift, shift)
+
+
+@pytest.mark.parametrize("m,n,k", [(3, 1, 32), (3, 17, 64), (16, 33, 2080), (17, 257, 96), (48, 65, 8224), (49, 31, 224),
+                                   (64, 300, 288), (65, 1, 32), (97, 700, 352), (129, 129, 608)])
+def test_picked_shape_exact(m, n, k):
+    """The shape that the size rule picks, at the smallest sizes and at
+    remainders of the tiles and stages."""
+    announce(f"gemm M={m} N={n} K={k}")
+    _check(m, n, k, m + n + k, shift=n % 2)
+
+
+@pytest.mark.parametrize("m", [5, 40, 100])
+def test_rows_and_columns_stay_apart(m):
+    """A NaN row of x reaches only its own outputs and a NaN scale only its
+    own column, also where K ends inside a stage."""
+    n, k = 70, 352
+    packed, scales, x, _ = _case(m, n, k, 7 * m)
+    ref = oracle.gemv(packed, scales, x, n, k).view(np.uint16)
+    xb, sb = x.copy(), scales.copy()
+    xb[1] = np.nan
+    sb[33, 0] = 0x7E00
+    announce(f"gemm NaN row and column M={m}")
+    y = to_host(gpu_gemv(to_dev(packed), to_dev(sb), to_dev(xb)), np.uint16)
+    keep_r, keep_c = np.arange(m) != 1, np.arange(n) != 33
+    assert np.array_equal(y[np.ix_(keep_r, keep_c)], ref[np.ix_(keep_r, keep_c)])
+    assert np.isnan(y[1].view(np.float16)).all() and np.isnan(y[:, 33].view(np.float16)).all()
+
+
+def test_prompt_list_of_many_linears_exact():
+    """70 independent linears and a dependent one at M = 66: more than one
+    launch's worth of descriptors, in one call, bit for bit."""
+    import torch
+
+    from paper_2412_15803_amd import wq
+
+    m, lins, refs = 66, [], []
+    announce("gemm list of 71 linears at M=66")
+    for i in range(70):
+        n, k = (64 if i == 8 else 1 + 37 * (i % 9)), 32 * (1 + i % 5)
+        packed, scales, x, sd = _case(m, n, k, 1000 + i, lo=-7, hi=-6)
+        lins.append((to_dev(packed), sd, to_dev(x), torch.empty((m, n), dtype=torch.float16, device="cuda:0")))
+        refs.append(oracle.gemv(packed, scales, x, n, k))
+    # Outputs are multiples of 2^-7 below 2^7, so this sum of 64 is exact too.
+    packed, scales, _, sd = _case(m, 40, 64, 2000, lo=-5, hi=-5)
+    lins.append((to_dev(packed), sd, lins[8][3], torch.empty((m, 40), dtype=torch.float16, device="cuda:0")))
+    refs.append(oracle.gemv(packed, scales, refs[8], 40, 64))
+    wq.wq_decode_linears(lins, m=m)
+    torch.cuda.synchronize()
+    for (_, _, _, y), ref in zip(lins, refs):
+        assert np.array_equal(to_host(y, np.uint16), ref.view(np.uint16))
