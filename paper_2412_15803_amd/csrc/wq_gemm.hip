@@ -140,6 +140,26 @@ __device__ __forceinline__ half8 dequant8_small(uint32_t w, half2v s20, half2v m
     return __builtin_bit_cast(half8, r);
 }
 
+// Rows of 16-byte chunks in LDS: chunk ch of a row lies at position ch ^
+// place(row), so that a matrix-core read is free of bank conflicts (64 banks
+// of 4 bytes).  A 16-byte-per-lane read is served 16 lanes at a time, lanes
+// 0-3, 12-15 and 20-27 together, then 4-11, 16-19 and 28-31, and so on; with
+// lane 16 c + li reading row li, each such set is all 16 rows, rows 0-3 and
+// 12-15 at one chunk and rows 4-11 at the next lane group's chunk, which
+// differs in one of the low bits only.  So the top bit of place() tells the
+// two sets of rows apart, the bits below it the rows of a set.  Rows of 256
+// bytes or more start on the same bank and take 16 positions; of 128 bytes,
+// on two, and take 8 for each pair.  (With row & 7 in its place every read
+// of a 128-byte row took 8 extra cycles, of a 256-byte row 4; 12 to 25% of
+// the LDS cycles.)
+template <int ROW_BYTES>
+__device__ __forceinline__ int place(int row) {
+    static_assert(ROW_BYTES == 128 || ROW_BYTES >= 256, "chunk rows");
+    const int mid = ((row >> 2) ^ (row >> 3)) & 1;  // rows 4-11
+    const int high = (row >> 3) & 1;
+    return ROW_BYTES == 128 ? mid << 2 | high << 1 | (row >> 1 & 1) : mid << 3 | high << 2 | (row & 3);
+}
+
 template <int TM, int TN, int NW, int KW, int XK, int CK, int W>
 struct Cfg {
     static constexpr int kWaves = NW * KW;
@@ -161,7 +181,7 @@ struct Cfg {
     static constexpr int RedBytes = KW > 1 ? kWaves * TM * TN * 1024 : 0;  // partial tiles, afterwards
     static constexpr int LdsBytes = RunBytes > RedBytes ? RunBytes : RedBytes;
     static_assert(XBytes % 1024 == 0, "x loads are whole");
-    static_assert(W >= 2, "the next window is complete before the last stage of a window");
+    static_assert(W == 2 || W == 4, "the next window is complete before the last stage of a window");
     static_assert(CSlotBytes % 1024 == 0 && SBytes % 1024 == 0, "slot loads are whole");
     static_assert(CK == XK || (CK == kStageK && QS <= 2), "code slots");
 };
@@ -217,8 +237,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
         for (int i = 0; i < NX; ++i) {
             const int ld = (wn * NX + i) % C::XLoads;       // load index in the stage
             const int r = lane / XCH, ph = lane % XCH;      // row within the load, LDS chunk
-            const int row7 = (ld * XR + r) & 7;
-            const int src = ph ^ row7;
+            const int src = ph ^ place<XK * 2>(ld * XR + r);
             const bool ok = st < se && k0 + 8 * src < ng * kGroup;
             const uint32_t voff = ok ? (uint32_t)r * xrow_bytes + (uint32_t)src * 16u : kOutOffset;
             const uint32_t soff = st < se ? (uint32_t)(ld * XR) * xrow_bytes + (uint32_t)k0 * 2u : 0u;
@@ -230,7 +249,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     constexpr int CR = 64 / CCH;      // rows per load
     auto issue_codes = [&](int st, int q, int i) {
         const int r = lane / CCH, ph = lane % CCH;
-        const int src = CK == kStageK ? ph ^ (r & 7) : ph;
+        const int src = CK == kStageK ? ph ^ place<128>(i * CR + r) : ph;
         const uint32_t voff = st < se ? ((uint32_t)r * (uint32_t)ng + (uint32_t)src) * 16u : kOutOffset;
         const uint32_t soff =
             st < se ? (uint32_t)((wrow + i * CR) * ng + st * kStageGroups + q * CCH) * 16u : 0u;
@@ -243,9 +262,12 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     // been loaded when it is read.
     constexpr int SP = W;             // 16-byte pieces per row
     constexpr int SR = 64 / SP;       // rows per load
+    // Piece pc of a row lies at position pc ^ splace(row): 16 rows of 16 W
+    // bytes cover the banks once per piece.
+    auto splace = [](int row) { return W == 4 ? (row >> 2) & 3 : (row >> 3) & 1; };
     auto issue_scales = [&](int w) {
         const int g0 = (sb + w * W) * kStageGroups;
-        const int r = lane / SP, pc = lane % SP;
+        const int r = lane / SP, pc = lane % SP ^ splace(r);
         const int left = (se - sb) - w * W;  // stages of this wave's range in the window
         const bool ok = left >= pc && (16 * TN % SR == 0 || r < 16 * TN);
 #pragma unroll
@@ -269,19 +291,28 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
 #pragma unroll
         for (int t = 0; t < WPL; ++t) {
             const int ch = h * 16 + WPL * c + t;
-            const uint32_t off = xlds + buf * C::XBytes + (uint32_t)li * (XK * 2) + (uint32_t)((ch ^ (li & 7)) * 16);
+            const uint32_t off = xlds + buf * C::XBytes + (uint32_t)li * (XK * 2) + (uint32_t)((ch ^ place<XK * 2>(li)) * 16);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
                 fa[slot][i][t] = *at<const half8>(off + i * 16 * XK * 2);
         }
     };
-    // The lane's scale of group g of row 16 tt + li of a stage (`it` stages
-    // into the range); zero past the row and past the range.
-    auto read_scale = [&](int tt, int g, int it) {
+    // The lane's scales of group g of a stage (`it` stages into the range), of
+    // row 16 tt + li: an LDS address and a mask, zero past the row and past
+    // the range (opaque, so that the reads stay unconditional).
+    struct ScaleAt {
+        uint32_t addr, keep;
+    };
+    auto scale_at = [&](int g, int it) {
         const uint32_t pos = (uint32_t)(it * kStageGroups + g) + odd;
-        const uint32_t sa = slds + ((pos / (8 * W)) & 1u) * C::SBytes + (uint32_t)li * C::SRow + (pos % (8 * W)) * 2u;
-        const uint32_t v = *at<const uint16_t>(sa + tt * 16 * C::SRow);
-        return sb + it < se && (sb + it) * kStageGroups + g < ng ? v : 0u;
+        const uint32_t pc = (pos / 8) % W ^ (uint32_t)splace(li);
+        ScaleAt s{slds + ((pos / (8 * W)) & 1u) * C::SBytes + (uint32_t)li * C::SRow + pc * 16 + (pos % 8) * 2u,
+                  sb + it < se && (sb + it) * kStageGroups + g < ng ? 0xFFFFu : 0u};
+        asm("" : "+v"(s.keep));
+        return s;
+    };
+    auto read_scale = [&](const ScaleAt& s, int tt) {
+        return (uint32_t)*at<const uint16_t>(s.addr + tt * 16 * C::SRow) & s.keep;
     };
     auto multiply = [&](auto small, const uint32_t* wd, uint32_t sv, int slot, int tt) {
         const half2v sc = as_h2(sv | (sv << 16));
@@ -319,14 +350,16 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
         };
         uint32_t s[TN][2];
         auto read_scales = [&](int it) {
+            const ScaleAt sa[2] = {scale_at(c, it), scale_at(4 + c, it)};
             uint32_t mx = 0;
 #pragma unroll
             for (int tt = 0; tt < TN; ++tt)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    s[tt][h] = read_scale(tt, 4 * h + c, it);
-                    mx = max(mx, s[tt][h] & 0x7FFFu);
-                }
+                for (int h = 0; h < 2; ++h) s[tt][h] = read_scale(sa[h], tt);
+#pragma unroll
+            for (int tt = 0; tt < TN; ++tt)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) mx = max(mx, s[tt][h] & 0x7FFFu);
             return mx;
         };
         auto read_tile = [&](Tile& T, int tt) {
@@ -334,7 +367,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int g = 4 * h + c;
-                const uint32_t ca = clds + row * 128 + (uint32_t)((g ^ (li & 7)) * 16);
+                const uint32_t ca = clds + row * 128 + (uint32_t)((g ^ place<128>(li)) * 16);
                 const u32x4 v = *at<const u32x4>(ca);
                 T.w[h][0] = v.x; T.w[h][1] = v.y; T.w[h][2] = v.z; T.w[h][3] = v.w;
             }
@@ -456,11 +489,12 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 const int w0 = q * (XK / 8) + WPL * c;
                 auto load_at = [&](int t) {
                     const int ch = WPL * c + t;
-                    const uint32_t off = xlds + buf * C::XBytes + (uint32_t)li * (XK * 2) + (uint32_t)((ch ^ (li & 7)) * 16);
+                    const uint32_t off = xlds + buf * C::XBytes + (uint32_t)li * (XK * 2) + (uint32_t)((ch ^ place<XK * 2>(li)) * 16);
 #pragma unroll
                     for (int i = 0; i < TM; ++i)
                         fa[0][i][t] = *at<const half8>(off + i * 16 * XK * 2);
                 };
+                const ScaleAt sa = scale_at(w0 / 4, it);
                 uint32_t wd[TN][WPL];
                 half2v sc[TN];
 #pragma unroll
@@ -473,7 +507,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                         const u32x2 v = *at<const u32x2>(ca);
                         wd[tt][0] = v.x; wd[tt][1] = v.y;
                     }
-                    const uint32_t sv = read_scale(tt, w0 / 4, it);
+                    const uint32_t sv = read_scale(sa, tt);
                     sc[tt] = as_h2(sv | (sv << 16));
                 }
                 load_at(0);
