@@ -227,6 +227,11 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     const int64_t wrow = row0 + wn * 16 * TN;                                        // this wave's first row
 
     // ---- loads.  Lane offsets within a load; wave-uniform parts are scalar.
+    // Past the wave's range the buffer is empty: zeros arrive.
+    auto in_range = [&](u32x4 d, int st) {
+        d.z = st < se ? d.z : 0u;
+        return d;
+    };
     // x: one load covers XR rows of an x stage, 16-byte chunks XOR-placed by row.
     constexpr int XCH = XK / 8;       // chunks per row
     constexpr int XR = 64 / XCH > 0 ? 64 / XCH : 1;
@@ -238,10 +243,10 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
             const int ld = (wn * NX + i) % C::XLoads;       // load index in the stage
             const int r = lane / XCH, ph = lane % XCH;      // row within the load, LDS chunk
             const int src = ph ^ place<XK * 2>(ld * XR + r);
-            const bool ok = st < se && k0 + 8 * src < ng * kGroup;
-            const uint32_t voff = ok ? (uint32_t)r * xrow_bytes + (uint32_t)src * 16u : kOutOffset;
-            const uint32_t soff = st < se ? (uint32_t)(ld * XR) * xrow_bytes + (uint32_t)k0 * 2u : 0u;
-            dma16(dx, voff, __builtin_amdgcn_readfirstlane(soff), xlds + buf * C::XBytes + ld * 1024);
+            const uint32_t voff =
+                k0 + 8 * src < ng * kGroup ? (uint32_t)r * xrow_bytes + (uint32_t)src * 16u : kOutOffset;
+            const uint32_t soff = (uint32_t)(ld * XR) * xrow_bytes + (uint32_t)k0 * 2u;
+            dma16(in_range(dx, st), voff, __builtin_amdgcn_readfirstlane(soff), xlds + buf * C::XBytes + ld * 1024);
         }
     };
     // Codes of slot q (CK deep) of stage st, load i: 1024 / (CK / 2) rows.
@@ -250,10 +255,9 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     auto issue_codes = [&](int st, int q, int i) {
         const int r = lane / CCH, ph = lane % CCH;
         const int src = CK == kStageK ? ph ^ place<128>(i * CR + r) : ph;
-        const uint32_t voff = st < se ? ((uint32_t)r * (uint32_t)ng + (uint32_t)src) * 16u : kOutOffset;
-        const uint32_t soff =
-            st < se ? (uint32_t)((wrow + i * CR) * ng + st * kStageGroups + q * CCH) * 16u : 0u;
-        dma16<CK == kStageK ? kCpolNonTemporal : kCpolDefault>(dw, voff, __builtin_amdgcn_readfirstlane(soff), clds + q * C::CSlotBytes + i * 1024);
+        const uint32_t voff = ((uint32_t)r * (uint32_t)ng + (uint32_t)src) * 16u;
+        const uint32_t soff = (uint32_t)((wrow + i * CR) * ng + st * kStageGroups + q * CCH) * 16u;
+        dma16<CK == kStageK ? kCpolNonTemporal : kCpolDefault>(in_range(dw, st), voff, __builtin_amdgcn_readfirstlane(soff), clds + q * C::CSlotBytes + i * 1024);
     };
     // Scale window `w` (W stages from sb + W w): 16-byte pieces of each row,
     // from the dword holding the row's first scale of the window.  Where that
@@ -277,6 +281,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
         }
     };
     const uint32_t odd = (spar + (uint32_t)((wrow + li) * ng)) & 1u;  // 16 ng is even: the same for every tile
+    const bool shifted = ((spar | (uint32_t)ng) & 1u) != 0;           // some row is odd
 
     float4v acc[TM][TN];
 #pragma unroll
@@ -297,40 +302,50 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 fa[slot][i][t] = *at<const half8>(off + i * 16 * XK * 2);
         }
     };
-    // The lane's scales of group g of a stage (`it` stages into the range), of
-    // row 16 tt + li: an LDS address and a mask, zero past the row and past
-    // the range (opaque, so that the reads stay unconditional).
-    struct ScaleAt {
-        uint32_t addr, keep;
+    // The lane's scale of group g (0..7) of a stage, `it` stages into the range,
+    // of row li; the other tiles' lie 16 rows on.
+    auto scale_addr = [&](int g, int it) {
+        const uint32_t pos = (uint32_t)g + odd;
+        const uint32_t piece = (uint32_t)it + pos / 8;
+        return slds + ((piece / W) & 1u) * C::SBytes + (uint32_t)li * C::SRow + (piece % W ^ (uint32_t)splace(li)) * 16 +
+               (pos % 8) * 2u;
     };
-    auto scale_at = [&](int g, int it) {
-        const uint32_t pos = (uint32_t)(it * kStageGroups + g) + odd;
-        const uint32_t pc = (pos / 8) % W ^ (uint32_t)splace(li);
-        ScaleAt s{slds + ((pos / (8 * W)) & 1u) * C::SBytes + (uint32_t)li * C::SRow + pc * 16 + (pos % 8) * 2u,
-                  sb + it < se && (sb + it) * kStageGroups + g < ng ? 0xFFFFu : 0u};
-        asm("" : "+v"(s.keep));
-        return s;
+    auto read_scale = [&](uint32_t addr, int tt) {
+        return (uint32_t)*at<const uint16_t>(addr + tt * 16 * C::SRow);
     };
-    auto read_scale = [&](const ScaleAt& s, int tt) {
-        return (uint32_t)*at<const uint16_t>(s.addr + tt * 16 * C::SRow) & s.keep;
+    // Some of the stage's groups lie past the row or past the range: their
+    // scales count as zero.
+    auto cut = [&](int it) { return sb + it >= se || (sb + it + 1) * kStageGroups > ng; };
+    auto keep_group = [&](int g, int it) {
+        return sb + it < se && (sb + it) * kStageGroups + g < ng ? 0xFFFFu : 0u;
     };
-    auto multiply = [&](auto small, const uint32_t* wd, uint32_t sv, int slot, int tt) {
-        const half2v sc = as_h2(sv | (sv << 16));
+    // What a lane's scales are used as: themselves, and times 2^20 and -8 for
+    // the short dequantization (two at once, in the halves).
+    struct Scales {
+        half2v s, s20, m8;
+    };
+    auto scales_of = [&](uint32_t pair) {
         const half2v k1024 = {(_Float16)1024.0f, (_Float16)1024.0f};
         const half2v km8 = {(_Float16)-8.0f, (_Float16)-8.0f};
-        const half2v s20 = sc * k1024 * k1024, m8s = sc * km8;
+        const half2v s = as_h2(pair);
+        return Scales{s, s * k1024 * k1024, s * km8};
+    };
+    // Multiplies of tile tt with the part of x in `slot`; the scale is half h
+    // of its pair.
+    auto multiply = [&](auto small, const uint32_t* wd, const Scales& sc, int h, int slot, int tt) {
+        auto both = [&](half2v v) { return half2v{v[h], v[h]}; };
 #pragma unroll
         for (int t = 0; t < WPL; ++t) {
             half8 fb;
-            if constexpr (decltype(small)::value) fb = dequant8_small(wd[t], s20, m8s);
-            else fb = dequant8(wd[t], sc);
+            if constexpr (decltype(small)::value) fb = dequant8_small(wd[t], both(sc.s20), both(sc.m8));
+            else fb = dequant8(wd[t], both(sc.s));
 #pragma unroll
             for (int i = 0; i < TM; ++i)
                 acc[i][tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[slot][i][t], fb, acc[i][tt], 0, 0, 0);
         }
     };
     // Whether every lane's scales allow the short dequantization.
-    auto all_small = [&](uint32_t mx) { return __builtin_amdgcn_ballot_w64(mx >= kSmallScale) == 0; };
+    auto all_small = [&](uint32_t mx) { return __builtin_amdgcn_ballot_w64(max(mx & 0xFFFFu, mx >> 16) >= kSmallScale) == 0; };
     using Small = std::integral_constant<bool, true>;
     using Any = std::integral_constant<bool, false>;
 
@@ -348,19 +363,23 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
         struct Tile {
             uint32_t w[2][4];
         };
-        uint32_t s[TN][2];
+        uint32_t pair[TN];  // scales of both halves
         auto read_scales = [&](int it) {
-            const ScaleAt sa[2] = {scale_at(c, it), scale_at(4 + c, it)};
-            uint32_t mx = 0;
+            const uint32_t a0 = scale_addr(c, it);
+            const uint32_t a1 = shifted ? scale_addr(4 + c, it) : a0 + 8;
+#pragma unroll
+            for (int tt = 0; tt < TN; ++tt) pair[tt] = read_scale(a0, tt) | read_scale(a1, tt) << 16;
+            if (cut(it)) {
+                const uint32_t keep = keep_group(c, it) | keep_group(4 + c, it) << 16;
+#pragma unroll
+                for (int tt = 0; tt < TN; ++tt) pair[tt] &= keep;
+            }
+            typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+            u16x2 mx = {0, 0};
 #pragma unroll
             for (int tt = 0; tt < TN; ++tt)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) s[tt][h] = read_scale(sa[h], tt);
-#pragma unroll
-            for (int tt = 0; tt < TN; ++tt)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) mx = max(mx, s[tt][h] & 0x7FFFu);
-            return mx;
+                mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, pair[tt] & 0x7FFF7FFFu));
+            return __builtin_bit_cast(uint32_t, mx);
         };
         auto read_tile = [&](Tile& T, int tt) {
             const uint32_t row = 16 * tt + li;
@@ -405,7 +424,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                         tile_read_done(T[tt & 1]);
                         refill(st + 1, tt);
 #pragma unroll
-                        for (int h = 0; h < HS; ++h) multiply(sm, T[tt & 1].w[h], s[tt][h], h, tt);
+                        for (int h = 0; h < HS; ++h) multiply(sm, T[tt & 1].w[h], scales_of(pair[tt]), h, h, tt);
                     }
                 };
                 if (small) body(Small{});
@@ -446,14 +465,14 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                         }
                         tile_read_done(T[tt]);
                         if (tt < TH) refill(st + 1, tt);
-                        multiply(sm, T[tt].w[0], s[tt][0], 0, tt);
+                        multiply(sm, T[tt].w[0], scales_of(pair[tt]), 0, 0, tt);
                     }
                 };
                 auto second = [&](auto sm) {
 #pragma unroll
                     for (int tt = 0; tt < TN; ++tt) {
                         if (tt >= TH) refill(st + 1, tt);
-                        multiply(sm, T[tt].w[1], s[tt][1], 0, tt);
+                        multiply(sm, T[tt].w[1], scales_of(pair[tt]), 1, 0, tt);
                     }
                 };
                 if (small) first(Small{});
@@ -494,7 +513,8 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                     for (int i = 0; i < TM; ++i)
                         fa[0][i][t] = *at<const half8>(off + i * 16 * XK * 2);
                 };
-                const ScaleAt sa = scale_at(w0 / 4, it);
+                const uint32_t sa = scale_addr(w0 / 4, it);
+                const uint32_t keep = cut(it) ? keep_group(w0 / 4, it) : 0xFFFFu;
                 uint32_t wd[TN][WPL];
                 half2v sc[TN];
 #pragma unroll
@@ -507,7 +527,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                         const u32x2 v = *at<const u32x2>(ca);
                         wd[tt][0] = v.x; wd[tt][1] = v.y;
                     }
-                    const uint32_t sv = read_scale(sa, tt);
+                    const uint32_t sv = read_scale(sa, tt) & keep;
                     sc[tt] = as_h2(sv | (sv << 16));
                 }
                 load_at(0);
