@@ -89,6 +89,8 @@ struct Params {
     int32_t pages_per_chunk;  // block-table entries one chunk can use
     int32_t pages_lds;        // bytes of LDS before the wave states
     int32_t xcd_local;        // nonzero: pairs are placed by XCD (xcd_pair)
+    int32_t seqs;
+    int32_t units;            // nonzero: chunks follow the lengths (unit_of), at most this many per kv head
     float c;            // scale * log2(e): scores in log2 units
 };
 
@@ -173,7 +175,108 @@ __device__ __forceinline__ void fold_pair(State& st) {
     st.m = mx;
 }
 
-template <int G>
+// ------------------------------------------------- chunks by the lengths
+//
+// With several sequences whose lengths differ, chunks of one fixed length
+// leave most workgroups empty and the longest sequence's as the end of the
+// launch: 40 sequences of 100 to 6000 tokens, 8 kv heads, took 112 us in
+// chunks of 4096 tokens, at 27% of the bandwidth (52 us now; equal lengths,
+// 16 x 4096, 49 to 51 us either way).  The lengths are on the
+// device, so every wave of the split kernel works the split out for itself,
+// from registers: the shortest chunk length T (of 16 candidates, multiples
+// of 64) that cuts all sequences into at most `units` chunks per kv head, the
+// number that the workspace has room for.  Unit u is then a chunk of one
+// sequence, the sequences in order, each cut into equal chunks.
+constexpr int kMaxSeqsByLength = 1024;
+constexpr int kCandidates = 16;
+constexpr int kMinUnitChunk = 256;  // tokens
+
+struct Unit {
+    int seq, len, chunk, first, count;  // sequence, its length, chunk of it; its first unit and number of units
+};
+
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2, 3
+    return v;
+}
+
+__device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, 63); }
+
+// max(1, ceil(len / t)) for len <= 2^22: a quotient estimate is off by one at
+// most.
+__device__ __forceinline__ int chunks_of(int len, int t) {
+    const int a = len + t - 1;
+    int q = (int)((float)a * __builtin_amdgcn_rcpf((float)t));
+    const int r = a - q * t;
+    q += r >= t ? 1 : r < 0 ? -1 : 0;
+    return max(1, q);
+}
+
+// Unit u of the launch; false past the last one.
+__device__ __forceinline__ bool unit_of(const Params& p, int u, Unit& out) {
+    const int lane = threadIdx.x & 63;
+    const int per = (p.seqs + 63) / 64;  // lane i has sequences [i per, (i + 1) per)
+    const int s0 = min(lane * per, p.seqs), s1 = min(s0 + per, p.seqs);
+    auto length = [&](int s) {
+        const int len = p.lens[s];
+        return bad_length(p, len) ? 0 : len;
+    };
+    const int len0 = s0 < s1 ? length(s0) : 0;
+    auto len_of = [&](int s) { return s == s0 ? len0 : length(s); };
+    int sum = 0;
+    for (int s = s0; s < s1; ++s) sum += len_of(s);
+    const int total = last_lane(wave_inclusive_scan(sum));
+    auto count = [&](int t) {
+        int n = 0;
+        for (int s = s0; s < s1; ++s) n += chunks_of(len_of(s), t);
+        return n;
+    };
+    // Any T of at least total / (units - seqs) leaves sum(len / T + 1) at
+    // most `units`, so the last candidate always fits; the number of chunks
+    // falls with T.
+    const int lo = max(kMinUnitChunk, (total + p.units - 1) / p.units);
+    const int hi = max(lo, (total + p.units - p.seqs - 1) / (p.units - p.seqs));
+    auto candidate = [&](int j) { return (lo + (hi - lo) / (kCandidates - 1) * j + 63) / 64 * 64; };
+    int below = -1, at = kCandidates - 1;  // candidate `below` does not fit, `at` does
+    int t = (hi + 63) / 64 * 64;
+    while (at - below > 1) {
+        const int j = (at + below) / 2;
+        const int c = candidate(j);
+        if (last_lane(wave_inclusive_scan(count(c))) <= p.units) {
+            at = j;
+            t = c;
+        } else {
+            below = j;
+        }
+    }
+    const int mine = count(t);
+    int first = wave_inclusive_scan(mine) - mine;
+    const uint64_t owner = __builtin_amdgcn_ballot_w64(u >= first && u < first + mine);
+    if (owner == 0) return false;
+    // The owning lane walks its sequences.
+    int s = s0, len = len0, n = chunks_of(len0, t);
+    if (u >= first && u < first + mine) {
+        while (u >= first + n) {
+            first += n;
+            len = length(++s);
+            n = chunks_of(len, t);
+        }
+    }
+    const int from = __builtin_ctzll(owner);
+    out.seq = __builtin_amdgcn_readlane(s, from);
+    out.len = __builtin_amdgcn_readlane(len, from);
+    out.first = __builtin_amdgcn_readlane(first, from);
+    out.count = __builtin_amdgcn_readlane(n, from);
+    out.chunk = u - out.first;
+    return true;
+}
+
+template <int G, bool BY_LENGTH>
 __global__ __launch_bounds__(kThreads) void split_kernel(const Params p) {
     extern __shared__ __align__(16) unsigned char smem[];
     int* sh_pages = reinterpret_cast<int*>(smem);
@@ -187,7 +290,25 @@ __global__ __launch_bounds__(kThreads) void split_kernel(const Params p) {
     // pair's XCD, as does the merge of its heads, so the merge reads the
     // partial results from that XCD's L2 instead of from memory.
     int chunk, seq_kv;
-    if (p.xcd_local) {
+    int chunk_tokens = p.chunk;
+    int64_t slot0 = 0;  // partial results of this workgroup's first head
+    if constexpr (BY_LENGTH) {
+        // Consecutive workgroups take the kv heads of one unit: with 8 of
+        // them, every unit of a kv head runs on one XCD.
+        Unit un;
+        if (!unit_of(p, blockIdx.x / p.hkv, un)) return;
+        chunk = un.chunk;
+        const int kv = blockIdx.x % p.hkv;
+        seq_kv = un.seq * p.hkv + kv;
+        chunk_tokens = ((un.len + un.count - 1) / un.count + kChunkQuantum - 1) / kChunkQuantum * kChunkQuantum;
+        slot0 = (int64_t)(un.first + chunk) * p.hq + (int64_t)kv * G;
+        // The merge finds a head's units in the head's output row, which it
+        // then overwrites.
+        if (chunk == 0 && (int)threadIdx.x < G) {
+            int2* info = reinterpret_cast<int2*>(p.out + ((int64_t)un.seq * p.hq + (int64_t)kv * G + threadIdx.x) * kD);
+            *info = make_int2(un.first, un.count);
+        }
+    } else if (p.xcd_local) {
         const int x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
         seq_kv = x + kXcds * (i / p.splits);
         chunk = i % p.splits;
@@ -203,7 +324,7 @@ __global__ __launch_bounds__(kThreads) void split_kernel(const Params p) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int log2_page = p.log2_page;
     const int page_mask = (1 << log2_page) - 1;
-    const int c0 = chunk * p.chunk;
+    const int c0 = chunk * chunk_tokens;
     const int first_page = c0 >> log2_page;
 
     // One round trip for the length, the query vectors and the block-table
@@ -220,7 +341,7 @@ __global__ __launch_bounds__(kThreads) void split_kernel(const Params p) {
         qv[g][3] = as_h2(t.w);
     }
     const int32_t* trow = p.table + (int64_t)s * p.max_pages + first_page;
-    const int table_left = (int)min<int64_t>(p.pages_per_chunk, p.max_pages - first_page);
+    const int table_left = (int)min<int64_t>(min(p.pages_per_chunk, (chunk_tokens >> log2_page) + 2), p.max_pages - first_page);
     for (int i = tid; i < table_left; i += kThreads) sh_pages[i] = trow[i];
     __syncthreads();
 
@@ -235,7 +356,7 @@ __global__ __launch_bounds__(kThreads) void split_kernel(const Params p) {
     int bad = 0;
 
     // This wave's tokens: [wbase, wbase + wtok) intersected with [0, len).
-    const int wtok = p.chunk / kWaves;
+    const int wtok = chunk_tokens / kWaves;
     const int wbase = c0 + wave * wtok;
     const int nvalid = min(max(len - wbase, 0), wtok);
     const int nblk = (nvalid + kBlockTokens - 1) / kBlockTokens;
@@ -375,7 +496,7 @@ __global__ __launch_bounds__(kThreads) void split_kernel(const Params p) {
         if (p.splits == 1) {
             p.out[(head0 + g) * kD + d] = l != l ? kHalfNaN : to_half_bits(acc / l);
         } else {
-            const int64_t slot = (head0 + g) * p.splits + chunk;
+            const int64_t slot = BY_LENGTH ? slot0 + g : (head0 + g) * p.splits + chunk;
             p.part_acc[slot * kD + d] = acc;
             if (d == 0) p.part_ml[slot] = make_float2(mx, l);
         }
@@ -389,6 +510,7 @@ __global__ __launch_bounds__(kThreads) void split_kernel(const Params p) {
 // with the length (only chunks below the launch's split count, all inside
 // the workspace), so short sequences take one round trip.  The eight slot
 // states are then merged through LDS.
+template <bool BY_LENGTH>
 __global__ __launch_bounds__(kThreads) void merge_kernel(const Params p) {
     constexpr int kCols = kD / 4;             // 32 four-dim columns
     constexpr int kSlots = kThreads / kCols;  // 8 chunk slots
@@ -399,7 +521,11 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(const Params p) {
     const int tid = threadIdx.x;
     const int slot = tid / kCols, cq = tid % kCols;
     int64_t head = blockIdx.x;  // seq * hq + h
-    if (p.xcd_local) {  // the heads of pair x + 8 j run on XCD x
+    if constexpr (BY_LENGTH) {  // consecutive workgroups take the kv heads, as the split kernel's do
+        const int group = p.hq / p.hkv;
+        const int kv = blockIdx.x % p.hkv, i = blockIdx.x / p.hkv;
+        head = (int64_t)(i / group) * p.hq + (int64_t)kv * group + i % group;
+    } else if (p.xcd_local) {  // the heads of pair x + 8 j run on XCD x
         const int group = p.hq / p.hkv;
         const int x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
         const int pair = x + kXcds * (i / group);
@@ -407,25 +533,34 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(const Params p) {
     }
     const int s = (int)(head / p.hq);
     uint16_t* o = p.out + head * kD;
-    const float2* ml = p.part_ml + head * p.splits;
-    const float4* pa = reinterpret_cast<const float4*>(p.part_acc + head * p.splits * kD) + cq;
+    // Chunk c of the head lies `step` slots after chunk c - 1; at most `most` of them.
+    int64_t base_slot = head * p.splits, step = 1;
+    int most = p.splits, have = 0;
+    if constexpr (BY_LENGTH) {
+        const int2 info = *reinterpret_cast<const int2*>(o);
+        base_slot = (int64_t)info.x * p.hq + head % p.hq;
+        step = p.hq;
+        most = have = info.y;
+    }
+    const float2* ml = p.part_ml + base_slot;
+    const float4* pa = reinterpret_cast<const float4*>(p.part_acc + base_slot * kD) + cq;
 
     const int len = p.lens[s];
     float m = -INFINITY, l = 0.0f;
     float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    int n = p.splits;  // chunks that hold data; known once the length arrives
+    int n = most;  // chunks that hold data; known once the length arrives
     for (int base = slot; base < n; base += kSlots * kBatch) {
         float2 h[kBatch];
         float4 v[kBatch];
 #pragma unroll
         for (int j = 0; j < kBatch; ++j) {
-            const int c = min(base + j * kSlots, p.splits - 1);
+            const int64_t c = min(base + j * kSlots, most - 1) * step;
             h[j] = ml[c];
-            v[j] = pa[(int64_t)c * kCols];
+            v[j] = pa[c * kCols];
         }
         if (base == slot) {
             if (bad_length(p, len) || len == 0) break;
-            n = (len + p.chunk - 1) / p.chunk;
+            n = have ? have : (len + p.chunk - 1) / p.chunk;
         }
         float mx = m;
 #pragma unroll
@@ -481,6 +616,8 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(const Params p) {
 struct Plan {
     int64_t chunk;
     int64_t splits;
+    int64_t units;     // nonzero: chunks by the lengths, at most this many per kv head
+    int64_t max_chunk; // tokens of the longest chunk
     size_t ml_offset;  // bytes of part_acc
     size_t ws_bytes;
 };
@@ -496,6 +633,14 @@ int64_t target_blocks() {
     return v > 0 ? v : 512;
 }
 
+constexpr int64_t kMaxWhole = 192;
+constexpr int64_t kByLengthChunk = 512;
+
+bool by_length() {
+    const char* e = getenv("WQ_ATTN_BY_LENGTH");
+    return !e || strtol(e, nullptr, 10) != 0;
+}
+
 // Chunk length: a multiple of 64 tokens that gives the split launch about
 // target_blocks() workgroups (what the chip holds at once, so there is a
 // single round of them), at most kMaxChunk tokens; with sequences of at most
@@ -506,7 +651,23 @@ Plan make_plan(int64_t seqs, int64_t hq, int64_t hkv, int64_t max_seq_len) {
     int64_t chunk = (len + want - 1) / want;
     chunk = (chunk + kChunkQuantum - 1) / kChunkQuantum * kChunkQuantum;
     chunk = std::min<int64_t>(std::max<int64_t>(chunk, kChunkQuantum), kMaxChunk);
-    Plan pl{chunk, (len + chunk - 1) / chunk, 0, 0};
+    // One workgroup takes a short sequence whole: the second launch would cost
+    // more than it saves (24 / 8 heads, one sequence: 192 tokens 6.3 us against
+    // 7.2 us, 256 tokens 7.9 against 7.4).
+    if (len <= kMaxWhole) chunk = (len + kChunkQuantum - 1) / kChunkQuantum * kChunkQuantum;
+    Plan pl{chunk, (len + chunk - 1) / chunk, 0, chunk, 0, 0};
+    // Several sequences in chunks of at least kByLengthChunk tokens: chunks
+    // follow the lengths (which costs two more round trips), in the same
+    // workspace.
+    if (seqs > 1 && seqs <= kMaxSeqsByLength && seqs * len <= INT32_MAX / 2 && pl.splits > 1 && chunk >= kByLengthChunk &&
+        by_length()) {
+        pl.units = seqs * pl.splits;
+        // Six query heads or more take over 256 registers: one workgroup per
+        // CU, so no more of them than CUs while that cuts every sequence.
+        if (hq / hkv >= 6) pl.units = std::min(pl.units, std::max(2 * seqs, 256 / hkv));
+        const int64_t hi = (seqs * len + pl.units - seqs - 1) / (pl.units - seqs);
+        pl.max_chunk = (std::max<int64_t>(hi, kMinUnitChunk) + 63) / 64 * 64;
+    }
     if (pl.splits > 1) {
         pl.ml_offset = (size_t)(seqs * hq * pl.splits * kD * 4);
         pl.ws_bytes = pl.ml_offset + (size_t)(seqs * hq * pl.splits * 8);
@@ -516,12 +677,15 @@ Plan make_plan(int64_t seqs, int64_t hq, int64_t hkv, int64_t max_seq_len) {
 
 template <int G>
 hipError_t launch_split(const Params& p, int64_t blocks, size_t lds, hipStream_t stream) {
-    hipLaunchKernelGGL(split_kernel<G>, dim3((unsigned)blocks), dim3(kThreads), lds, stream, p);
+    if (p.units)
+        hipLaunchKernelGGL((split_kernel<G, true>), dim3((unsigned)blocks), dim3(kThreads), lds, stream, p);
+    else
+        hipLaunchKernelGGL((split_kernel<G, false>), dim3((unsigned)blocks), dim3(kThreads), lds, stream, p);
     return hipGetLastError();
 }
 
 hipError_t launch(const Params& p, int group, int64_t seqs, hipStream_t stream) {
-    const int64_t blocks = seqs * p.hkv * p.splits;
+    const int64_t blocks = p.hkv * (p.units ? (int64_t)p.units : seqs * p.splits);
     const size_t lds = (size_t)p.pages_lds + (size_t)kWaves * group * (kD + 2) * 4;
     hipError_t e;
     switch (group) {
@@ -535,7 +699,10 @@ hipError_t launch(const Params& p, int group, int64_t seqs, hipStream_t stream) 
         default: e = launch_split<8>(p, blocks, lds, stream); break;
     }
     if (e != hipSuccess || p.splits == 1) return e;
-    hipLaunchKernelGGL(merge_kernel, dim3((unsigned)(seqs * p.hq)), dim3(kThreads), 0, stream, p);
+    if (p.units)
+        hipLaunchKernelGGL((merge_kernel<true>), dim3((unsigned)(seqs * p.hq)), dim3(kThreads), 0, stream, p);
+    else
+        hipLaunchKernelGGL((merge_kernel<false>), dim3((unsigned)(seqs * p.hq)), dim3(kThreads), 0, stream, p);
     return hipGetLastError();
 }
 
@@ -662,7 +829,7 @@ wq_status wq_paged_attention(const uint16_t* q, const uint16_t* k_cache, const u
     const int group = (int)(num_q_heads / num_kv_heads);
     const int log2_page = log2_of(page_size);
     // Pages a chunk can touch: it may start inside a page.
-    const int64_t pages_per_chunk = (pl.chunk >> log2_page) + 2;
+    const int64_t pages_per_chunk = (pl.max_chunk >> log2_page) + 2;
 
     Params p{};
     p.q = q;
@@ -686,6 +853,8 @@ wq_status wq_paged_attention(const uint16_t* q, const uint16_t* k_cache, const u
     p.pages_lds = (int32_t)((pages_per_chunk * 4 + 15) / 16 * 16);
     p.c = (float)((double)scale * 1.4426950408889634);  // log2(e)
     // Place pairs by XCD only when every XCD gets the same number of them.
+    p.seqs = (int32_t)num_seqs;
+    p.units = (int32_t)pl.units;
     p.xcd_local = pl.splits > 1 && (num_seqs * num_kv_heads) % kXcds == 0 && xcd_placement();
 
     (void)hipGetLastError();
