@@ -128,83 +128,97 @@ def _check(status: int) -> None:
 
 
 # ------------------------------------------------------------- marshalling
+#
+# A small call's time is this code's (a 512 x 512 linear runs about 2 us on
+# the device), so a tensor is looked at once, with plain attribute reads, and
+# pointers and the stream are passed as integers (the declared argument types
+# turn them into C values).
 
-def _dev_tensor(t, name, dtypes, shape):
+_torch = None
+_WORDS = _HALVES = _FLOATS = _INTS = _BYTES = ()
+_raw_stream = None
+
+
+def _load_torch():
+    global _torch, _WORDS, _HALVES, _FLOATS, _INTS, _BYTES, _raw_stream
     import torch
 
-    if not isinstance(t, torch.Tensor):
+    _WORDS = (torch.int32, torch.uint32)
+    _HALVES = (torch.float16, torch.int16, torch.uint16)
+    _FLOATS = (torch.float32,)
+    _INTS = (torch.int32,)
+    _BYTES = (torch.uint8,)
+    # The current stream's handle without building a Stream object.
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _torch = torch
+    return torch
+
+
+def _dev_tensor(t, name, dtypes, shape):
+    """The device address of `t` after the checks that every argument gets."""
+    if not isinstance(t, _torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor (got {t.device})")
     if t.dtype not in dtypes:
         raise TypeError(f"{name} has dtype {t.dtype}, expected one of {dtypes}")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous (row-major)")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream, device):
-    import torch
-
-    if stream is None:
-        stream = torch.cuda.current_stream(device)
-    return ctypes.c_void_p(stream.cuda_stream)
-
-
-def _word_dtypes():
-    import torch
-
-    return (torch.int32, torch.uint32)
-
-
-def _half_dtypes():
-    import torch
-
-    return (torch.float16, torch.int16, torch.uint16)
+def _stream(stream, t):
+    """The handle of `stream`, or of the current stream of the device of `t`."""
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(t.get_device())
+    return _torch.cuda.current_stream(t.device).cuda_stream
 
 
 def wq_pack(w, packed_w, scales, group: int = GROUP, stream=None) -> None:
     """Quantize fp32 w [N, K] into packed_w [N, K/8] (int32/uint32 words) and
     scales [N, K/32] (fp16), both preallocated on the same device."""
-    import torch
-
+    _torch or _load_torch()
     if w.dim() != 2:
         raise ValueError("w must be 2-D [N, K]")
     n, k = w.shape
-    pw = _dev_tensor(w, "w", (torch.float32,), (n, k))
-    pp = _dev_tensor(packed_w, "packed_w", _word_dtypes(), (n, k // 8))
-    ps = _dev_tensor(scales, "scales", _half_dtypes(), (n, k // group if group else 0))
-    _check(lib().wq_pack(pw, pp, ps, n, k, group, _stream(stream, w.device)))
+    pw = _dev_tensor(w, "w", _FLOATS, (n, k))
+    pp = _dev_tensor(packed_w, "packed_w", _WORDS, (n, k // 8))
+    ps = _dev_tensor(scales, "scales", _HALVES, (n, k // group if group else 0))
+    _check((_lib or lib()).wq_pack(pw, pp, ps, n, k, group, _stream(stream, w)))
 
 
 def wq_gemv(packed_w, scales, x, y, group: int = GROUP, stream=None) -> None:
     """y [M, N] = x [M, K] . dequant(packed_w, scales)^T (fp16 in, fp16 out)."""
+    _torch or _load_torch()
     if x.dim() != 2 or packed_w.dim() != 2:
         raise ValueError("x must be [M, K] and packed_w [N, K/8]")
     m, k = x.shape
     n = packed_w.shape[0]
-    pp = _dev_tensor(packed_w, "packed_w", _word_dtypes(), (n, k // 8))
-    ps = _dev_tensor(scales, "scales", _half_dtypes(), (n, k // group if group else 0))
-    px = _dev_tensor(x, "x", _half_dtypes(), (m, k))
-    py = _dev_tensor(y, "y", _half_dtypes(), (m, n))
-    _check(lib().wq_gemv(pp, ps, px, py, n, k, m, group, _stream(stream, x.device)))
+    pp = _dev_tensor(packed_w, "packed_w", _WORDS, (n, k // 8))
+    ps = _dev_tensor(scales, "scales", _HALVES, (n, k // group if group else 0))
+    px = _dev_tensor(x, "x", _HALVES, (m, k))
+    py = _dev_tensor(y, "y", _HALVES, (m, n))
+    _check((_lib or lib()).wq_gemv(pp, ps, px, py, n, k, m, group, _stream(stream, x)))
 
 
 def make_linear_array(linears, m: int, group: int = GROUP):
     """Marshal a sequence of (packed_w, scales, x, y) tensor tuples into a
     ctypes wq_linear array."""
+    _torch or _load_torch()
     arr = (WqLinear * len(linears))()
     for i, (packed_w, scales, x, y) in enumerate(linears):
         if x.dim() != 2 or x.shape[0] != m:
             raise ValueError(f"linear {i}: x must be [M={m}, K]")
         k = x.shape[1]
         n = packed_w.shape[0]
-        arr[i].packed_w = _dev_tensor(packed_w, f"linears[{i}].packed_w", _word_dtypes(), (n, k // 8)).value
-        arr[i].scales = _dev_tensor(scales, f"linears[{i}].scales", _half_dtypes(), (n, k // group if group else 0)).value
-        arr[i].x = _dev_tensor(x, f"linears[{i}].x", _half_dtypes(), (m, k)).value
-        arr[i].y = _dev_tensor(y, f"linears[{i}].y", _half_dtypes(), (m, n)).value
+        arr[i].packed_w = _dev_tensor(packed_w, f"linears[{i}].packed_w", _WORDS, (n, k // 8))
+        arr[i].scales = _dev_tensor(scales, f"linears[{i}].scales", _HALVES, (n, k // group if group else 0))
+        arr[i].x = _dev_tensor(x, f"linears[{i}].x", _HALVES, (m, k))
+        arr[i].y = _dev_tensor(y, f"linears[{i}].y", _HALVES, (m, n))
         arr[i].N = n
         arr[i].K = k
     return arr
@@ -215,16 +229,16 @@ def wq_decode_linears(linears, m: int = 1, group: int = GROUP, stream=None, _arr
     sequence of (packed_w, scales, x, y) tuples; a prebuilt array from
     make_linear_array may be passed as _array to skip re-marshalling."""
     arr = _array if _array is not None else make_linear_array(linears, m, group)
-    device = linears[0][2].device
-    _check(lib().wq_decode_linears(arr, len(arr), m, group, _stream(stream, device)))
+    _torch or _load_torch()
+    _check((_lib or lib()).wq_decode_linears(arr, len(arr), m, group, _stream(stream, linears[0][2])))
 
 
 def wq_decode_linears_noalloc(linears, m: int = 1, group: int = GROUP, stream=None, _array=None) -> None:
     """wq_decode_linears through the entry point that allocates nothing (its
     plan lives in the library's fixed per-device array; see include/wq.h)."""
     arr = _array if _array is not None else make_linear_array(linears, m, group)
-    device = linears[0][2].device
-    _check(lib().wq_decode_linears_noalloc(arr, len(arr), m, group, _stream(stream, device)))
+    _torch or _load_torch()
+    _check((_lib or lib()).wq_decode_linears_noalloc(arr, len(arr), m, group, _stream(stream, linears[0][2])))
 
 
 # ------------------------------------------------------- paged attention
@@ -253,30 +267,28 @@ def paged_attention(q, k_cache, v_cache, block_table, seq_lens, out, scale: floa
     caches [pages, HKV, P, D] (fp16), block_table [S, max_pages] and
     seq_lens [S] (int32), all on one device.  `workspace` is a uint8 device
     tensor from paged_workspace (allocated here when omitted)."""
-    import torch
-
+    _torch or _load_torch()
     if q.dim() != 3 or k_cache.dim() != 4:
         raise ValueError("q must be [S, HQ, D] and the caches [pages, HKV, P, D]")
     num_seqs, hq, d = q.shape
     num_pages, hkv, page, d2 = k_cache.shape
     max_pages = block_table.shape[1] if block_table.dim() == 2 else 0
-    pq = _dev_tensor(q, "q", _half_dtypes(), (num_seqs, hq, d))
-    pk = _dev_tensor(k_cache, "k_cache", _half_dtypes(), (num_pages, hkv, page, d2))
-    pv = _dev_tensor(v_cache, "v_cache", _half_dtypes(), (num_pages, hkv, page, d2))
-    pt = _dev_tensor(block_table, "block_table", (torch.int32,), (num_seqs, max_pages))
-    pl = _dev_tensor(seq_lens, "seq_lens", (torch.int32,), (num_seqs,))
-    po = _dev_tensor(out, "out", _half_dtypes(), (num_seqs, hq, d))
+    pq = _dev_tensor(q, "q", _HALVES, (num_seqs, hq, d))
+    pk = _dev_tensor(k_cache, "k_cache", _HALVES, (num_pages, hkv, page, d2))
+    pv = _dev_tensor(v_cache, "v_cache", _HALVES, (num_pages, hkv, page, d2))
+    pt = _dev_tensor(block_table, "block_table", _INTS, (num_seqs, max_pages))
+    pl = _dev_tensor(seq_lens, "seq_lens", _INTS, (num_seqs,))
+    po = _dev_tensor(out, "out", _HALVES, (num_seqs, hq, d))
     if workspace is None:
         workspace = paged_workspace(q, max_seq_len, hkv)
     if workspace is not None:
-        if workspace.device != q.device or workspace.dtype != torch.uint8 or not workspace.is_contiguous():
+        if workspace.device != q.device or workspace.dtype not in _BYTES or not workspace.is_contiguous():
             raise ValueError("workspace must be a contiguous uint8 tensor on the device of q")
-        pw, nw = ctypes.c_void_p(workspace.data_ptr()), workspace.numel()
+        pw, nw = workspace.data_ptr(), workspace.numel()
     else:
         pw, nw = None, 0
-    _check(lib().wq_paged_attention(pq, pk, pv, pt, pl, po, num_seqs, hq, hkv, d, page, num_pages,
-                                    max_pages, max_seq_len, float(scale), pw, nw,
-                                    _stream(stream, q.device)))
+    _check((_lib or lib()).wq_paged_attention(pq, pk, pv, pt, pl, po, num_seqs, hq, hkv, d, page, num_pages,
+                                              max_pages, max_seq_len, float(scale), pw, nw, _stream(stream, q)))
 
 
 # ------------------------------------------------------- fused decode chain
@@ -286,6 +298,7 @@ def make_fused_array(linears, group: int = GROUP):
     prologue (PROLOGUE_*), norm_weight, eps, residual into a ctypes
     wq_fused_linear array.  x is [K] ([2K] for PROLOGUE_SILU_MUL), y and
     residual [N], norm_weight [K]; 1-D or [1, n] tensors are accepted."""
+    _torch or _load_torch()
     arr = (WqFusedLinear * len(linears))()
     for i, d in enumerate(linears):
         packed_w, scales, x, y = d["packed_w"], d["scales"], d["x"], d["y"]
@@ -293,15 +306,15 @@ def make_fused_array(linears, group: int = GROUP):
         n = packed_w.shape[0]
         k = packed_w.shape[1] * 8
         xk = 2 * k if pro == PROLOGUE_SILU_MUL else k
-        arr[i].packed_w = _dev_tensor(packed_w, f"linears[{i}].packed_w", _word_dtypes(), (n, k // 8)).value
-        arr[i].scales = _dev_tensor(scales, f"linears[{i}].scales", _half_dtypes(), (n, k // group)).value
-        arr[i].x = _dev_tensor(x.reshape(-1), f"linears[{i}].x", _half_dtypes(), (xk,)).value
-        arr[i].y = _dev_tensor(y.reshape(-1), f"linears[{i}].y", _half_dtypes(), (n,)).value
+        arr[i].packed_w = _dev_tensor(packed_w, f"linears[{i}].packed_w", _WORDS, (n, k // 8))
+        arr[i].scales = _dev_tensor(scales, f"linears[{i}].scales", _HALVES, (n, k // group))
+        arr[i].x = _dev_tensor(x.reshape(-1), f"linears[{i}].x", _HALVES, (xk,))
+        arr[i].y = _dev_tensor(y.reshape(-1), f"linears[{i}].y", _HALVES, (n,))
         norm = d.get("norm_weight")
-        arr[i].norm_weight = _dev_tensor(norm, f"linears[{i}].norm_weight", _half_dtypes(), (k,)).value \
+        arr[i].norm_weight = _dev_tensor(norm, f"linears[{i}].norm_weight", _HALVES, (k,)) \
             if norm is not None else None
         res = d.get("residual")
-        arr[i].residual = _dev_tensor(res.reshape(-1), f"linears[{i}].residual", _half_dtypes(), (n,)).value \
+        arr[i].residual = _dev_tensor(res.reshape(-1), f"linears[{i}].residual", _HALVES, (n,)) \
             if res is not None else None
         arr[i].N = n
         arr[i].K = k
@@ -314,12 +327,10 @@ def wq_fused_linears(linears, argmax=None, group: int = GROUP, stream=None, _arr
     """Run a chain of fused linears in order (see make_fused_array); when
     `argmax` (a device int32 tensor of one element) is given, the index of
     the largest element of the last linear's y is written to it."""
-    import torch
-
+    _torch or _load_torch()
     arr = _array if _array is not None else make_fused_array(linears, group)
-    device = linears[0]["x"].device
-    pa = _dev_tensor(argmax.reshape(-1), "argmax", (torch.int32,), (1,)) if argmax is not None else None
-    _check(lib().wq_fused_linears(arr, len(arr), pa, group, _stream(stream, device)))
+    pa = _dev_tensor(argmax.reshape(-1), "argmax", _INTS, (1,)) if argmax is not None else None
+    _check((_lib or lib()).wq_fused_linears(arr, len(arr), pa, group, _stream(stream, linears[0]["x"])))
 
 
 def wq_fused_check(device=None, stream=None) -> None:
@@ -327,8 +338,8 @@ def wq_fused_check(device=None, stream=None) -> None:
     device gave up since the last check (a bounded wait ran out)."""
     import torch
 
-    device = torch.device("cuda", torch.cuda.current_device()) if device is None else device
-    _check(lib().wq_fused_check(_stream(stream, device)))
+    stream = torch.cuda.current_stream(device) if stream is None else stream
+    _check(lib().wq_fused_check(stream.cuda_stream))
 
 
 # ------------------------------------------------------- measurement probe
@@ -343,5 +354,5 @@ def stream_read(buf, sink, stream=None) -> None:
     nbytes = buf.numel() * buf.element_size()
     if sink.device != buf.device or sink.dtype not in (torch.int32, torch.uint32) or sink.numel() < 1024:
         raise ValueError("sink must be a device int32 tensor of at least 1024 elements")
-    _check(lib().wq_stream_read(ctypes.c_void_p(buf.data_ptr()), nbytes, ctypes.c_void_p(sink.data_ptr()),
-                                _stream(stream, buf.device)))
+    _torch or _load_torch()
+    _check(lib().wq_stream_read(buf.data_ptr(), nbytes, sink.data_ptr(), _stream(stream, buf)))
