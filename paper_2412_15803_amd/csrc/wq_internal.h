@@ -18,7 +18,7 @@ wq_status record_error(wq_status st, const char* message);
 // recorded as the thread's last error message for entry point `fn`.
 wq_status hip_error(const char* fn, hipError_t e);
 
-// Quantize + pack: one thread per (row, group).
+// Quantize + pack.
 hipError_t launch_pack(const float* w, uint32_t* packed, uint16_t* scales,
                        int64_t n, int64_t k, hipStream_t stream);
 

@@ -15,50 +15,83 @@ constexpr int kTargetWaves = 256 * 8;  // 256 CUs x 8 waves
 
 // --------------------------------------------------------------- quantize
 //
-// One thread per (row, group), grid-stride.  Bit-exact: IEEE fp32 division
-// (__fdiv_rn), round-to-nearest-even fp32->fp16 keeping subnormals, rintf
-// (ties to even), clamp to [0, 15].
-__global__ __launch_bounds__(kBlock) void pack_kernel(const float* __restrict__ w,
-                                                      uint32_t* __restrict__ packed,
-                                                      uint16_t* __restrict__ scales, int64_t n, int64_t k) {
-    const int64_t ng = k / kGroup;
-    const int64_t total = n * ng;
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < total; t += stride) {
-        const int64_t row = t / ng;
-        const int64_t g = t - row * ng;
-        const float4* src = reinterpret_cast<const float4*>(w + row * k + g * kGroup);
-        float v[kGroup];
+// HBM-bound when the arithmetic stays out of the way: 4.5625 bytes per weight
+// against 32 IEEE divisions per group, which alone took most of the time of
+// one thread per group (28672 x 4096: 95 us, 5.6 TB/s; 84.5 us, 6.3 TB/s now).  Now eight lanes share
+// a group: a wave-wide 16-byte load covers eight consecutive groups, four of
+// them per wave are in flight, and a code costs about seven instructions: the
+// quotient is w times the reciprocal of the scale, and only where it lies
+// within 2^-16 of a half-integer, where the product could round to the other
+// side (its error is below 16 * 1.5 * 2^-23 < 2^-18 for quotients up to 16), is
+// the IEEE division made.  Bit-exact: round-to-nearest-even fp32->fp16
+// keeping subnormals, ties to even, clamp to [0, 15].
+constexpr int kPackLoads = 4;                  // loads per wave, eight groups each
+constexpr int kPackGroups = 8 * kPackLoads;    // groups per wave
+
+__device__ __forceinline__ float max_over_8(float v) {
+    auto mx = [&](int t) { v = fmaxf(v, __builtin_bit_cast(float, t)); };
+    mx(__builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, false));   // lane ^ 1
+    mx(__builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, false));   // lane ^ 2
+    mx(__builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x141, 0xF, 0xF, false));  // 7 - lane
+    return v;
+}
+
+__global__ __launch_bounds__(kBlock) void pack_kernel(const float* __restrict__ w, uint32_t* __restrict__ packed,
+                                                      uint16_t* __restrict__ scales, int64_t groups) {
+    typedef float float4v __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t stride = (int64_t)gridDim.x * kWavesPerBlock * kPackGroups;
+    int64_t g0 = ((int64_t)blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave)) * kPackGroups;
+    for (; g0 < groups; g0 += stride) {
+        float4v v[kPackLoads];
 #pragma unroll
-        for (int i = 0; i < kGroup / 4; ++i) {
-            const float4 f = src[i];
-            v[4 * i + 0] = f.x;
-            v[4 * i + 1] = f.y;
-            v[4 * i + 2] = f.z;
-            v[4 * i + 3] = f.w;
+        for (int i = 0; i < kPackLoads; ++i) {
+            const int64_t g = min(g0 + 8 * i + lane / 8, groups - 1);
+            v[i] = __builtin_nontemporal_load(gbl(reinterpret_cast<const float4v*>(w)) + g * 8 + lane % 8);
         }
-        float amax = 0.0f;
+        uint32_t half_word[kPackLoads], sbits[kPackLoads];
 #pragma unroll
-        for (int i = 0; i < kGroup; ++i) amax = fmaxf(amax, fabsf(v[i]));
-        const __half s16 = __float2half_rn(__fdiv_rn(amax, 7.0f));
-        const float s = __half2float(s16);
-        uint32_t words[4];
+        for (int i = 0; i < kPackLoads; ++i) {
+            const float amax = max_over_8(fmaxf(fmaxf(fabsf(v[i].x), fabsf(v[i].y)), fmaxf(fabsf(v[i].z), fabsf(v[i].w))));
+            const __half s16 = __float2half_rn(__fdiv_rn(amax, 7.0f));
+            const float s = __half2float(s16);
+            const float inv = s != 0.0f ? __builtin_amdgcn_rcpf(s) : 0.0f;
+            float q[4], off = 0.0f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            uint32_t word = 0;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                uint32_t code = 8;
-                if (s != 0.0f) {
-                    const float q = rintf(__fdiv_rn(v[8 * j + i], s)) + 8.0f;
-                    code = (uint32_t)fminf(fmaxf(q, 0.0f), 15.0f);
-                }
-                word |= code << (4 * i);
+            for (int e = 0; e < 4; ++e) {
+                const float t = v[i][e] * inv;
+                q[e] = rintf(t);
+                off = fmaxf(off, fabsf(t - q[e]));
             }
-            words[j] = word;
+            if (off > 0.5f - 0x1p-16f) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) q[e] = s != 0.0f ? rintf(__fdiv_rn(v[i][e], s)) : 0.0f;
+            }
+            // Four codes as one exact sum: (q_e + 8) 16^e.
+            float sum = 8.0f * 4369.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                sum = fmaf(__builtin_amdgcn_fmed3f(q[e], -8.0f, 7.0f), (float)(1 << (4 * e)), sum);
+            half_word[i] = (uint32_t)sum;
+            sbits[i] = __half_as_ushort(s16);
         }
-        reinterpret_cast<uint4*>(packed)[row * ng + g] = make_uint4(words[0], words[1], words[2], words[3]);
-        scales[row * ng + g] = __half_as_ushort(s16);
+        // Lanes 2j and 2j + 1 hold the halves of a word; the even lane stores
+        // it for the first of two loads, the odd lane for the second.
+#pragma unroll
+        for (int i = 0; i < kPackLoads; i += 2) {
+            const bool odd = lane & 1;
+            const uint32_t mine = odd ? half_word[i + 1] : half_word[i];
+            const uint32_t give = odd ? half_word[i] : half_word[i + 1];
+            const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)give, 0xB1, 0xF, 0xF, false);
+            const int64_t g = g0 + 8 * (i + odd) + lane / 8;
+            if (g < groups) gbl(packed)[g * 4 + lane % 8 / 2] = odd ? got | mine << 16 : mine | got << 16;
+        }
+        // Lane 8j + i stores the scale of group j of load i.
+        uint32_t sb = sbits[0];
+#pragma unroll
+        for (int i = 1; i < kPackLoads; ++i) sb = lane % 8 == i ? sbits[i] : sb;
+        const int64_t g = g0 + 8 * (lane % 8) + lane / 8;
+        if (lane % 8 < kPackLoads && g < groups) gbl(scales)[g] = (uint16_t)sb;
     }
 }
 
@@ -603,9 +636,10 @@ bool use_matrix_cores(int64_t m) {
 
 hipError_t launch_pack(const float* w, uint32_t* packed, uint16_t* scales, int64_t n, int64_t k,
                        hipStream_t stream) {
-    const int64_t threads = n * (k / kGroup);
-    const int64_t blocks = min((threads + kBlock - 1) / kBlock, (int64_t)1 << 20);
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, stream, w, packed, scales, n, k);
+    const int64_t groups = n * (k / kGroup);
+    const int64_t per_block = kWavesPerBlock * kPackGroups;
+    const int64_t blocks = min((groups + per_block - 1) / per_block, (int64_t)1 << 20);
+    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, stream, w, packed, scales, groups);
     return hipGetLastError();
 }
 
