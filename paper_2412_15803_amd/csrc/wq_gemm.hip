@@ -35,10 +35,12 @@
 // K order inside a 16 x 32 multiply: lane 16 c + li takes word t of its own
 // group for row li, and x's 8-element pieces are read in the same order.
 //
-// Measured on one MI355X (cold weights): 16384 x 3072 at M = 2048 204-217 us
-// = 950-1014 TFLOP/s (262 us with the tile kernel this replaced, which wrote
-// dequantized weights to LDS); 128256 x 3072 at M = 2048 1.48 ms; a 3B-class
-// step at M = 48 0.34 ms against 1.27 ms in passes of 16 rows.
+// Measured on one MI355X (cold weights; before = passes of 16 rows below
+// M = 65, a tile kernel that wrote dequantized weights to LDS above):
+//   16384 x 3072, M = 2048     188-193 us = 1070-1100 TFLOP/s (before 262-269)
+//   3B-class layers, M = 512   2.8 ms for 112 linears (before 8.0 ms)
+//   3B-class step, M = 48      470 us (before 1270)
+//   8B-class step, M = 8       707 us = 6.0 TB/s (before 866-879)
 #include <algorithm>
 #include <array>
 #include <cmath>
@@ -197,8 +199,16 @@ struct GemmArgs {
 };
 
 // One block: rows [row0, row0 + kRowsN) of W, rows [m0, m0 + kRowsM) of x.
+//
+// `turn` (one pass over W) is the scale window at which the block starts its
+// walk along K, round to the one before.  A block's rows are read one line at
+// the same column at a time; where K is a multiple of 8192 (code rows 4 KiB
+// apart) those lines share a few memory channels, and blocks that all start
+// at column 0 share the same few.  Measured at M = 8: 131072 x 8192 126 ->
+// 108 us; at K = 3072 and 14336, where rows spread by themselves, turning
+// gained nothing (0 to -2%).
 template <int TM, int TN, int NW, int KW, int XK, int CK, int W>
-__device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int64_t m0, lds_u8* lds) {
+__device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int64_t m0, int turn, lds_u8* lds) {
     using C = Cfg<TM, TN, NW, KW, XK, CK, W>;
     constexpr int QS = C::QS, NX = C::NX, NC = C::NC, NS = C::NS;
     constexpr int HS = XK >= 128 ? XK / 128 : 1;  // 128-deep parts of an x stage
@@ -212,6 +222,12 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     const int sb = wk * nst / KW, se = (wk + 1) * nst / KW;
     const int iters = (nst + KW - 1) / KW;  // of the longest range: the barriers are shared
     const int mrows = (int)min((int64_t)C::kRowsM, a.m - m0);
+    // Only whole windows can turn, and only rows whose scales start on a dword.
+    const int range = se - sb;
+    const bool turns = CK == kStageK && range > 0 && range % W == 0 && ng % 256 == 0 &&
+                       !(reinterpret_cast<uintptr_t>(a.scales) & 2);
+    const int start = sb + (turns ? turn * W % range : 0);
+    const int wrap = turns ? range : 0;  // what a stage past the end goes back by
     const uint32_t xrow_bytes = (uint32_t)ng * 64u;
     const u32x4 dw = make_desc(a.packed, (uint32_t)(a.n * ng * 16));
     // Scales are read in whole dwords: the descriptor starts at the dword
@@ -228,15 +244,15 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
 
     // ---- loads.  Lane offsets within a load; wave-uniform parts are scalar.
     // Past the wave's range the buffer is empty: zeros arrive.
-    auto in_range = [&](u32x4 d, int st) {
-        d.z = st < se ? d.z : 0u;
+    auto in_range = [&](u32x4 d, bool ok) {
+        d.z = ok ? d.z : 0u;
         return d;
     };
     // x: one load covers XR rows of an x stage, 16-byte chunks XOR-placed by row.
     constexpr int XCH = XK / 8;       // chunks per row
     constexpr int XR = 64 / XCH > 0 ? 64 / XCH : 1;
     static_assert(XCH <= 32 && (XR >= 2), "x rows per load");
-    auto issue_x = [&](int st, int q, int buf) {
+    auto issue_x = [&](int st, bool ok, int q, int buf) {
         const int k0 = st * kStageK + q * XK;
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
@@ -246,20 +262,20 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
             const uint32_t voff =
                 k0 + 8 * src < ng * kGroup ? (uint32_t)r * xrow_bytes + (uint32_t)src * 16u : kOutOffset;
             const uint32_t soff = (uint32_t)(ld * XR) * xrow_bytes + (uint32_t)k0 * 2u;
-            dma16(in_range(dx, st), voff, __builtin_amdgcn_readfirstlane(soff), xlds + buf * C::XBytes + ld * 1024);
+            dma16(in_range(dx, ok), voff, __builtin_amdgcn_readfirstlane(soff), xlds + buf * C::XBytes + ld * 1024);
         }
     };
     // Codes of slot q (CK deep) of stage st, load i: 1024 / (CK / 2) rows.
     constexpr int CCH = CK / 32;      // 16-byte chunks (groups) per row and slot
     constexpr int CR = 64 / CCH;      // rows per load
-    auto issue_codes = [&](int st, int q, int i) {
+    auto issue_codes = [&](int st, bool ok, int q, int i) {
         const int r = lane / CCH, ph = lane % CCH;
         const int src = CK == kStageK ? ph ^ place<128>(i * CR + r) : ph;
         const uint32_t voff = ((uint32_t)r * (uint32_t)ng + (uint32_t)src) * 16u;
         const uint32_t soff = (uint32_t)((wrow + i * CR) * ng + st * kStageGroups + q * CCH) * 16u;
-        dma16<CK == kStageK ? kCpolNonTemporal : kCpolDefault>(in_range(dw, st), voff, __builtin_amdgcn_readfirstlane(soff), clds + q * C::CSlotBytes + i * 1024);
+        dma16<CK == kStageK ? kCpolNonTemporal : kCpolDefault>(in_range(dw, ok), voff, __builtin_amdgcn_readfirstlane(soff), clds + q * C::CSlotBytes + i * 1024);
     };
-    // Scale window `w` (W stages from sb + W w): 16-byte pieces of each row,
+    // Scale window `w` of the walk (W stages from `st`): 16-byte pieces of each row,
     // from the dword holding the row's first scale of the window.  Where that
     // scale is the dword's upper half (`odd`), the row's scales sit one place
     // later: its last one is the first of the next window, which has long
@@ -269,10 +285,10 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     // Piece pc of a row lies at position pc ^ splace(row): 16 rows of 16 W
     // bytes cover the banks once per piece.
     auto splace = [](int row) { return W == 4 ? (row >> 2) & 3 : (row >> 3) & 1; };
-    auto issue_scales = [&](int w) {
-        const int g0 = (sb + w * W) * kStageGroups;
+    auto issue_scales = [&](int w, int st) {
+        const int g0 = st * kStageGroups;
         const int r = lane / SP, pc = lane % SP ^ splace(r);
-        const int left = (se - sb) - w * W;  // stages of this wave's range in the window
+        const int left = w * W < range ? se - st : min(se - st, 0);  // stages of the range from the window on
         const bool ok = left >= pc && (16 * TN % SR == 0 || r < 16 * TN);
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
@@ -315,10 +331,12 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     };
     // Some of the stage's groups lie past the row or past the range: their
     // scales count as zero.
-    auto cut = [&](int it) { return sb + it >= se || (sb + it + 1) * kStageGroups > ng; };
-    auto keep_group = [&](int g, int it) {
-        return sb + it < se && (sb + it) * kStageGroups + g < ng ? 0xFFFFu : 0u;
+    auto cut = [&](int it, int st) { return it >= range || (st + 1) * kStageGroups > ng; };
+    auto keep_group = [&](int g, int it, int st) {
+        return it < range && st * kStageGroups + g < ng ? 0xFFFFu : 0u;
     };
+    // The stage after `st`, and the one W on.
+    auto after = [&](int st, int by) { return st + by >= se ? st + by - wrap : st + by; };
     // What a lane's scales are used as: themselves, and times 2^20 and -8 for
     // the short dequantization (two at once, in the halves).
     struct Scales {
@@ -349,12 +367,12 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     using Small = std::integral_constant<bool, true>;
     using Any = std::integral_constant<bool, false>;
 
-    issue_x(sb, 0, 0);
-    issue_scales(0);
+    issue_x(start, range > 0, 0, 0);
+    issue_scales(0, start);
 #pragma unroll
     for (int q = 0; q < C::CSlots; ++q)
 #pragma unroll
-        for (int i = 0; i < NC; ++i) issue_codes(sb, q, i);
+        for (int i = 0; i < NC; ++i) issue_codes(start, range > 0, q, i);
 
     if constexpr (CK == kStageK) {
         // One slot of whole lines.  A tile's codes (both 128-deep halves) go
@@ -364,13 +382,13 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
             uint32_t w[2][4];
         };
         uint32_t pair[TN];  // scales of both halves
-        auto read_scales = [&](int it) {
+        auto read_scales = [&](int it, int st) {
             const uint32_t a0 = scale_addr(c, it);
             const uint32_t a1 = shifted ? scale_addr(4 + c, it) : a0 + 8;
 #pragma unroll
             for (int tt = 0; tt < TN; ++tt) pair[tt] = read_scale(a0, tt) | read_scale(a1, tt) << 16;
-            if (cut(it)) {
-                const uint32_t keep = keep_group(c, it) | keep_group(4 + c, it) << 16;
+            if (cut(it, st)) {
+                const uint32_t keep = keep_group(c, it, st) | keep_group(4 + c, it, st) << 16;
 #pragma unroll
                 for (int tt = 0; tt < TN; ++tt) pair[tt] &= keep;
             }
@@ -394,21 +412,22 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
         };
         // The reads of T have completed (the last one issued has).
         auto tile_read_done = [&](Tile& T) { asm volatile("" : "+v"(T.w[0][3]), "+v"(T.w[1][3])::"memory"); };
-        auto refill = [&](int st, int tt) {
-            issue_codes(st, 0, 2 * tt);
-            issue_codes(st, 0, 2 * tt + 1);
+        auto refill = [&](int st, bool ok, int tt) {
+            issue_codes(st, ok, 0, 2 * tt);
+            issue_codes(st, ok, 0, 2 * tt + 1);
         };
         if constexpr (QS == 1) {
-            for (int it = 0; it < iters; ++it) {
-                const int st = sb + it, buf = it & 1;
+            for (int it = 0, st = start; it < iters; ++it, st = after(st, 1)) {
+                const int next = after(st, 1), buf = it & 1;
+                const bool more = it + 1 < range;
                 wait_dma<2 * TN>();  // x and scales of the stage; codes may be in flight
                 block_sync<NW>();
-                issue_x(st + 1, 0, buf ^ 1);
+                issue_x(next, more, 0, buf ^ 1);
                 const bool win = it % W == 0;  // a scale window starts: load the next one
-                if (win) issue_scales(it / W + 1);
+                if (win) issue_scales(it / W + 1, after(st, W));
 #pragma unroll
                 for (int h = 0; h < HS; ++h) load_a(buf, h, h);
-                const bool small = all_small(read_scales(it));
+                const bool small = all_small(read_scales(it, st));
                 auto body = [&](auto sm) {
                     Tile T[2];
                     if (win) wait_dma<2 * (TN - 1) + NX + NS>();
@@ -422,7 +441,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                             read_tile(T[(tt + 1) & 1], tt + 1);
                         }
                         tile_read_done(T[tt & 1]);
-                        refill(st + 1, tt);
+                        refill(next, more, tt);
 #pragma unroll
                         for (int h = 0; h < HS; ++h) multiply(sm, T[tt & 1].w[h], scales_of(pair[tt]), h, h, tt);
                     }
@@ -435,16 +454,17 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
             // The first half of the tiles is refilled in the first x stage,
             // the others in the second.
             constexpr int TH = (TN + 1) / 2;
-            for (int it = 0; it < iters; ++it) {
-                const int st = sb + it;
+            for (int it = 0, st = start; it < iters; ++it, st = after(st, 1)) {
+                const int next = after(st, 1);
+                const bool more = it + 1 < range;
                 Tile T[TN];
                 if (it == 0) wait_dma<2 * TN>();
                 else wait_dma<2 * (TN - TH)>();
                 block_sync<NW>();
-                if (it % W == 0) issue_scales(it / W + 1);
-                issue_x(st, 1, 1);
+                if (it % W == 0) issue_scales(it / W + 1, after(st, W));
+                issue_x(st, it < range, 1, 1);
                 load_a(0, 0, 0);
-                const bool small = all_small(read_scales(it));
+                const bool small = all_small(read_scales(it, st));
                 auto first = [&](auto sm) {
                     // Newer than tile 0's codes: at most every other tile's and x.
                     if (it == 0) wait_dma<2 * (TN - 1) + NX>();
@@ -464,14 +484,14 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                             read_tile(T[tt + 1], tt + 1);
                         }
                         tile_read_done(T[tt]);
-                        if (tt < TH) refill(st + 1, tt);
+                        if (tt < TH) refill(next, more, tt);
                         multiply(sm, T[tt].w[0], scales_of(pair[tt]), 0, 0, tt);
                     }
                 };
                 auto second = [&](auto sm) {
 #pragma unroll
                     for (int tt = 0; tt < TN; ++tt) {
-                        if (tt >= TH) refill(st + 1, tt);
+                        if (tt >= TH) refill(next, more, tt);
                         multiply(sm, T[tt].w[1], scales_of(pair[tt]), 1, 0, tt);
                     }
                 };
@@ -479,7 +499,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 else first(Any{});
                 wait_dma<2 * TH>();  // x stage 1
                 block_sync<NW>();
-                issue_x(st + 1, 0, 0);
+                issue_x(next, more, 0, 0);
                 load_a(1, 0, 0);
                 if (small) second(Small{});
                 else second(Any{});
@@ -488,8 +508,9 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     } else {
         // One slot per x stage, each refilled for the next weight stage once
         // used: QS - 1 slots are always in flight.
-        for (int it = 0; it < iters; ++it) {
-            const int st = sb + it;
+        for (int it = 0, st = start; it < iters; ++it, st = after(st, 1)) {
+            const int next = after(st, 1);
+            const bool more = it + 1 < range;
 #pragma unroll
             for (int q = 0; q < QS; ++q) {
                 // The x stage's loads, issued before the previous x stage's
@@ -499,10 +520,10 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 block_sync<NW>();
                 const int buf = q & 1;
                 if (q == QS - 1) {
-                    issue_x(st + 1, 0, buf ^ 1);
+                    issue_x(next, more, 0, buf ^ 1);
                 } else {
-                    if (q == 0 && it % W == 0) issue_scales(it / W + 1);
-                    issue_x(st, q + 1, buf ^ 1);
+                    if (q == 0 && it % W == 0) issue_scales(it / W + 1, after(st, W));
+                    issue_x(st, it < range, q + 1, buf ^ 1);
                 }
                 // Words of the lane: WPL from word w0 of the stage's row.
                 const int w0 = q * (XK / 8) + WPL * c;
@@ -514,7 +535,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                         fa[0][i][t] = *at<const half8>(off + i * 16 * XK * 2);
                 };
                 const uint32_t sa = scale_addr(w0 / 4, it);
-                const uint32_t keep = cut(it) ? keep_group(w0 / 4, it) : 0xFFFFu;
+                const uint32_t keep = cut(it, st) ? keep_group(w0 / 4, it, st) : 0xFFFFu;
                 uint32_t wd[TN][WPL];
                 half2v sc[TN];
 #pragma unroll
@@ -544,7 +565,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-                for (int i = 0; i < NC; ++i) issue_codes(st + 1, q, i);
+                for (int i = 0; i < NC; ++i) issue_codes(next, more, q, i);
             }
         }
     }
@@ -625,7 +646,8 @@ __device__ __forceinline__ void run_tile(const GemmArgs& a, int b, int blocks_m,
     const int blocks_n = (int)((a.n + C::kRowsN - 1) / C::kRowsN);
     int bn = b, bm = 0;
     if (blocks_m > 1) tile_of(b, blocks_n, blocks_m, bn, bm);
-    gemm_block<TM, TN, NW, KW, XK, CK, W>(a, (int64_t)bn * C::kRowsN, (int64_t)bm * C::kRowsM, lds);
+    gemm_block<TM, TN, NW, KW, XK, CK, W>(a, (int64_t)bn * C::kRowsN, (int64_t)bm * C::kRowsM, blocks_m > 1 ? 0 : bn,
+                                          lds);
 }
 
 template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int OCC>
@@ -677,7 +699,7 @@ template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int OCC>
 __global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_list_kernel(const GemmList l) {
     using C = Cfg<TM, TN, NW, KW, XK, CK, W>;
     __shared__ __align__(16) uint8_t s_lds[C::LdsBytes];
-    const int b = xcd_run(blockIdx.x, gridDim.x);
+    const int b = blockIdx.x;
     int lo = 0, hi = l.count - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;
@@ -685,8 +707,12 @@ __global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_list_kernel(const Gem
         else hi = mid - 1;
     }
     const GemmArgs a{l.e[lo].packed, l.e[lo].scales, l.e[lo].x, l.e[lo].y, l.e[lo].n, l.e[lo].ng, l.m};
+    // First blocks are multiples of 8: every linear is dealt to all XCDs.
     const int blocks_m = (l.m + C::kRowsM - 1) / C::kRowsM;
-    run_tile<C, TM, TN, NW, KW, XK, CK, W>(a, b - l.e[lo].first_block, blocks_m, (lds_u8*)s_lds);
+    const int blocks = (int)((a.n + C::kRowsN - 1) / C::kRowsN) * blocks_m;
+    const int r = b - l.e[lo].first_block;
+    if (r >= blocks) return;
+    run_tile<C, TM, TN, NW, KW, XK, CK, W>(a, xcd_run(r, blocks), blocks_m, (lds_u8*)s_lds);
 }
 
 // ------------------------------------------------------------- dispatch
@@ -694,12 +720,12 @@ __global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_list_kernel(const Gem
 // The compiled block shapes: TM, TN, NW, KW, XK, CK, W and blocks per CU
 // that the registers are compiled for.
 #define WQ_GEMM_CONFIGS(X)        \
-    X(1, 2, 8, 1, 128, 256, 4, 2) \
+    X(1, 2, 4, 1, 128, 256, 4, 4) \
     X(1, 2, 4, 2, 128, 256, 2, 2) \
     X(1, 2, 2, 4, 128, 256, 2, 2) \
     X(1, 2, 1, 8, 128, 256, 2, 1) \
     X(1, 1, 1, 4, 128, 256, 2, 2) \
-    X(2, 4, 4, 1, 128, 256, 2, 2) \
+    X(2, 2, 8, 1, 128, 256, 4, 2) \
     X(2, 4, 2, 2, 128, 256, 2, 2) \
     X(2, 2, 2, 2, 128, 256, 2, 2) \
     X(2, 4, 1, 4, 128, 256, 2, 1) \
@@ -709,7 +735,7 @@ __global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_list_kernel(const Gem
     X(3, 2, 2, 2, 128, 256, 2, 2) \
     X(3, 2, 1, 4, 128, 256, 2, 1) \
     X(3, 1, 1, 4, 128, 256, 2, 1) \
-    X(4, 4, 4, 1, 128, 256, 2, 2) \
+    X(4, 2, 8, 1, 128, 256, 2, 2) \
     X(4, 2, 4, 1, 64, 64, 2, 4)   \
     X(4, 4, 2, 2, 128, 256, 2, 1) \
     X(4, 2, 2, 2, 64, 64, 2, 2)   \
@@ -788,7 +814,8 @@ double block_us(const Config& c, int64_t k, int resident) {
 
 // Estimated microseconds of a launch of `lin` (count linears) at m rows:
 // whole rounds of resident blocks and a last one with fewer per CU, or, for
-// several linears, an even spread of their blocks and the end of the longest.
+// several linears (longest K first), an even spread of their blocks and the
+// end of a short one, at least the longest alone.
 struct Shape {
     int64_t n, k;
 };
@@ -797,18 +824,19 @@ double launch_us(const Config& c, const Shape* lin, int count, int64_t m) {
     const int64_t bm = (m + c.rows_m - 1) / c.rows_m;
     const int64_t slots = (int64_t)kCus * c.occ;
     int64_t blocks = 0;
-    double work = 0.0, longest = 0.0, bytes = 0.0;
+    double work = 0.0, longest = 0.0, shortest = 1e30, bytes = 0.0;
     for (int i = 0; i < count; ++i) blocks += (lin[i].n + c.rows_n - 1) / c.rows_n * bm;
     const int resident = (int)std::min<int64_t>(c.occ, (blocks + kCus - 1) / kCus);
     for (int i = 0; i < count; ++i) {
         const double t = block_us(c, lin[i].k, resident);
         work += t * (double)((lin[i].n + c.rows_n - 1) / c.rows_n * bm);
-        longest = std::max(longest, t);
+        longest = std::max(longest, count > 1 ? block_us(c, lin[i].k, 1) : t);
+        shortest = std::min(shortest, t);
         bytes += (double)lin[i].n * lin[i].k * 0.5625;
     }
     double t;
     if (count > 1) {
-        t = std::max(longest, work / ((double)kCus * resident) + 0.5 * longest);
+        t = std::max(longest, work / ((double)kCus * resident) + 0.5 * shortest);
     } else {
         const int64_t full = blocks / slots, rest = blocks % slots;
         t = full * longest;
@@ -880,6 +908,8 @@ hipError_t launch_gemm(const uint32_t* packed, const uint16_t* scales, const uin
 }
 
 hipError_t launch_gemm_list(const wq_linear* lin, int count, int64_t m, hipStream_t stream) {
+    // Linears of one launch are independent, so their blocks may come in any
+    // order: the longest K first, and the launch ends on short blocks.
     for (int i0 = 0; i0 < count;) {
         std::array<Shape, kListEntries> s;
         const int n = std::min(count - i0, kListEntries);
@@ -891,12 +921,20 @@ hipError_t launch_gemm_list(const wq_linear* lin, int count, int64_t m, hipStrea
         int taken = 0;
         for (; taken < n; ++taken) {
             const wq_linear& w = lin[i0 + taken];
-            const int64_t more = blocks_of(c, w.N, m);
+            const int64_t more = (blocks_of(c, w.N, m) + 7) / 8 * 8;
             if (taken > 0 && blocks + more > INT32_MAX) break;
             l.e[taken] = GemmEntry{w.packed_w, w.scales, w.x, w.y, w.N, (int32_t)(w.K / kGroup), (int32_t)blocks};
             blocks += more;
         }
         l.count = taken;
+        std::sort(l.e, l.e + taken, [](const GemmEntry& a, const GemmEntry& b) {
+            return a.ng != b.ng ? a.ng > b.ng : a.first_block < b.first_block;
+        });
+        int64_t first = 0;
+        for (int i = 0; i < taken; ++i) {
+            l.e[i].first_block = (int32_t)first;
+            first += (blocks_of(c, l.e[i].n, m) + 7) / 8 * 8;
+        }
         const hipError_t e = c.list(l, blocks, stream);
         if (e != hipSuccess) return e;
         i0 += taken;

@@ -158,13 +158,17 @@ BatchPlan plan_batch_group(const wq_linear* lin, const Group& g, int64_t m, Plan
     DecodeEntry* ents = reinterpret_cast<DecodeEntry*>(out.data + bp.off_entries);
     const int rows = gemm_plan_rows(bp.config);
     const int64_t blocks_m = gemm_plan_blocks_m(bp.config, m);
+    for (int i = 0; i < count; ++i) fill_entry(ents[i], lin[g.begin + i]);
+    // The longest K first, so that the launch ends on short blocks (sorted
+    // in place, without allocating).
+    std::sort(ents, ents + count, [](const DecodeEntry& a, const DecodeEntry& b) {
+        return a.ng != b.ng ? a.ng > b.ng : a.packed != b.packed ? a.packed < b.packed : a.y < b.y;
+    });
     int64_t blocks = 0;
     for (int i = 0; i < count; ++i) {
-        const wq_linear& l = lin[g.begin + i];
         DecodeEntry& e = ents[i];
-        fill_entry(e, l);
         e.first_step = blocks;
-        e.steps = (l.N + rows - 1) / rows * blocks_m;
+        e.steps = (e.n + rows - 1) / rows * blocks_m;
         blocks += e.steps;
     }
     bp.blocks = blocks;
