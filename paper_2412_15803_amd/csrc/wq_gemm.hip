@@ -1,4 +1,4 @@
-// 4-bit GEMM on the matrix cores: y[M][N] = x[M][K] dequant(W)^T for M >= 3,
+// 4-bit GEMM on the matrix cores: y[M][N] = x[M][K] dequant(W)^T for M >= 2,
 // from a few concurrent sequences (one pass over the weights for up to 64
 // rows of x) to whole prompts.  Batching sequences is this library's
 // extension of the paper's batch-1 decoding; the tiling follows the
@@ -8,6 +8,16 @@
 // scale and rounded once to fp16 (relative error at most 2^-11 per weight;
 // |q - 8| s must stay below the fp16 range, i.e. scales below 8188), and
 // v_mfma_f32_16x16x32_f16 accumulates in fp32.
+//
+// Up to four rows of x (R = 4) a 16-row tile holds each row four times, once
+// for each lane group's words and zero elsewhere, so that after the four words
+// a tile's sums are those of single groups, in the lane that holds the group's
+// scale.  The codes then go to the matrix cores as they are (q 2^-20, exact
+// subnormals: 7 operations per word), starting from -8 2^-20 times the sums
+// of x, and the scale is applied in fp32.  Before, M = 2 ran on the vector
+// kernel (fp32 scales as well); 3B-class step at M = 2 342 -> 282 us, 8B-class
+// 778 -> 631, at M = 4 370 -> 293 and 831 -> 653 (against the step's earlier
+// kernel).  From M = 5 on two such tiles were 15-24% slower than one of 16.
 //
 // Loads.  Codes, scales and x all go straight into LDS (buffer loads with
 // the LDS destination, 16 bytes per lane), so the bytes in flight are bounded
@@ -142,6 +152,20 @@ __device__ __forceinline__ half8 dequant8_small(uint32_t w, half2v s20, half2v m
     return __builtin_bit_cast(half8, r);
 }
 
+// The codes alone, q 2^-20 as subnormals, or (q - 8) 2^-20; both are exact.
+template <bool CENTRED>
+__device__ __forceinline__ half8 codes8(uint32_t w) {
+    const half2v m8 = {(_Float16)-0x1p-17f, (_Float16)-0x1p-17f};
+    const uint32_t od = w & 0xF0F0F0F0u, ev = (w << 4) & 0xF0F0F0F0u;
+    u32x4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t t = __builtin_amdgcn_perm(od, ev, 0x0C000C00u | (uint32_t)((4 + j) << 16 | j));
+        r[j] = CENTRED ? __builtin_bit_cast(uint32_t, as_h2(t) + m8) : t;
+    }
+    return __builtin_bit_cast(half8, r);
+}
+
 // Rows of 16-byte chunks in LDS: chunk ch of a row lies at position ch ^
 // place(row), so that a matrix-core read is free of bank conflicts (64 banks
 // of 4 bytes).  A 16-byte-per-lane read is served 16 lanes at a time, lanes
@@ -162,14 +186,14 @@ __device__ __forceinline__ int place(int row) {
     return ROW_BYTES == 128 ? mid << 2 | high << 1 | (row >> 1 & 1) : mid << 3 | high << 2 | (row & 3);
 }
 
-template <int TM, int TN, int NW, int KW, int XK, int CK, int W>
+template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R>
 struct Cfg {
     static constexpr int kWaves = NW * KW;
     static constexpr int kThreads = kWaves * kWave;
-    static constexpr int kRowsM = 16 * TM;
+    static constexpr int kRowsM = R * TM;                // rows of x (a tile holds 16, or 4 in 4 places)
     static constexpr int kRowsN = 16 * TN * NW;
     static constexpr int QS = kStageK / XK;              // x stages per weight stage
-    static constexpr int XBytes = kRowsM * XK * 2;       // one x buffer
+    static constexpr int XBytes = 16 * TM * XK * 2;      // one x buffer
     static constexpr int XLoads = XBytes / 1024;         // x loads of a stage
     static constexpr int NX = (XLoads + NW - 1) / NW;    // per wave (the surplus repeats other loads)
     static constexpr int CSlots = kStageK / CK;
@@ -182,6 +206,7 @@ struct Cfg {
     static constexpr int RunBytes = KW * 2 * XBytes + kWaves * WaveBytes;
     static constexpr int RedBytes = KW > 1 ? kWaves * TM * TN * 1024 : 0;  // partial tiles, afterwards
     static constexpr int LdsBytes = RunBytes > RedBytes ? RunBytes : RedBytes;
+    static_assert(R == 16 || (R == 4 && XK == 128 && CK == kStageK), "x rows per tile");
     static_assert(XBytes % 1024 == 0, "x loads are whole");
     static_assert(W == 2 || W == 4, "the next window is complete before the last stage of a window");
     static_assert(CSlotBytes % 1024 == 0 && SBytes % 1024 == 0, "slot loads are whole");
@@ -207,9 +232,9 @@ struct GemmArgs {
 // at column 0 share the same few.  Measured at M = 8: 131072 x 8192 126 ->
 // 108 us; at K = 3072 and 14336, where rows spread by themselves, turning
 // gained nothing (0 to -2%).
-template <int TM, int TN, int NW, int KW, int XK, int CK, int W>
+template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R>
 __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int64_t m0, int turn, lds_u8* lds) {
-    using C = Cfg<TM, TN, NW, KW, XK, CK, W>;
+    using C = Cfg<TM, TN, NW, KW, XK, CK, W, R>;
     constexpr int QS = C::QS, NX = C::NX, NC = C::NC, NS = C::NS;
     constexpr int HS = XK >= 128 ? XK / 128 : 1;  // 128-deep parts of an x stage
     constexpr int WPL = XK >= 128 ? 4 : XK / 32;  // words per lane of a part
@@ -259,9 +284,11 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
             const int ld = (wn * NX + i) % C::XLoads;       // load index in the stage
             const int r = lane / XCH, ph = lane % XCH;      // row within the load, LDS chunk
             const int src = ph ^ place<XK * 2>(ld * XR + r);
+            // R = 4: row r of the load is x row r, kept for one lane group only.
+            const bool kept = R == 16 || src / 4 == ld % 4;
             const uint32_t voff =
-                k0 + 8 * src < ng * kGroup ? (uint32_t)r * xrow_bytes + (uint32_t)src * 16u : kOutOffset;
-            const uint32_t soff = (uint32_t)(ld * XR) * xrow_bytes + (uint32_t)k0 * 2u;
+                kept && k0 + 8 * src < ng * kGroup ? (uint32_t)r * xrow_bytes + (uint32_t)src * 16u : kOutOffset;
+            const uint32_t soff = (uint32_t)(R == 16 ? ld * XR : ld / 4 * 4) * xrow_bytes + (uint32_t)k0 * 2u;
             dma16(in_range(dx, ok), voff, __builtin_amdgcn_readfirstlane(soff), xlds + buf * C::XBytes + ld * 1024);
         }
     };
@@ -350,17 +377,54 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     };
     // Multiplies of tile tt with the part of x in `slot`; the scale is half h
     // of its pair.
+    float4v bias[TM];  // R = 4: -8 2^-20 times the sums of x over each group
     auto multiply = [&](auto small, const uint32_t* wd, const Scales& sc, int h, int slot, int tt) {
         auto both = [&](half2v v) { return half2v{v[h], v[h]}; };
+        constexpr bool fast = decltype(small)::value;
+        if constexpr (R == 4) {
+            float4v d[TM];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) d[i] = fast ? bias[i] : float4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int t = 0; t < WPL; ++t) {
+                const half8 fb = codes8<!fast>(wd[t]);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    d[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[slot][i][t], fb, d[i], 0, 0, 0);
+            }
+            const float s = (float)sc.s[h] * 0x1p20f;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[i][tt][v] = __builtin_fmaf(d[i][v], s, acc[i][tt][v]);
+            return;
+        }
 #pragma unroll
         for (int t = 0; t < WPL; ++t) {
             half8 fb;
-            if constexpr (decltype(small)::value) fb = dequant8_small(wd[t], both(sc.s20), both(sc.m8));
+            if constexpr (fast) fb = dequant8_small(wd[t], both(sc.s20), both(sc.m8));
             else fb = dequant8(wd[t], both(sc.s));
 #pragma unroll
             for (int i = 0; i < TM; ++i)
                 acc[i][tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[slot][i][t], fb, acc[i][tt], 0, 0, 0);
         }
+    };
+    // R = 4: the bias, and whether it is finite, i.e. x holds no infinity
+    // (which times q, less itself times 8, would be no number).
+    auto set_bias = [&] {
+        const _Float16 b = (_Float16)-0x1p-17f;
+        const half8 fb = {b, b, b, b, b, b, b, b};
+        float z = 0.0f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            bias[i] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int t = 0; t < WPL; ++t)
+                bias[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[0][i][t], fb, bias[i], 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) z = __builtin_fmaf(bias[i][v], 0.0f, z);
+        }
+        return __builtin_amdgcn_ballot_w64(z != z) == 0;
     };
     // Whether every lane's scales allow the short dequantization.
     auto all_small = [&](uint32_t mx) { return __builtin_amdgcn_ballot_w64(max(mx & 0xFFFFu, mx >> 16) >= kSmallScale) == 0; };
@@ -464,7 +528,10 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 if (it % W == 0) issue_scales(it / W + 1, after(st, W));
                 issue_x(st, it < range, 1, 1);
                 load_a(0, 0, 0);
-                const bool small = all_small(read_scales(it, st));
+                const uint32_t mx = read_scales(it, st);
+                bool small;
+                if constexpr (R == 4) small = set_bias();
+                else small = all_small(mx);
                 auto first = [&](auto sm) {
                     // Newer than tile 0's codes: at most every other tile's and x.
                     if (it == 0) wait_dma<2 * (TN - 1) + NX>();
@@ -501,6 +568,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 block_sync<NW>();
                 issue_x(next, more, 0, 0);
                 load_a(1, 0, 0);
+                if constexpr (R == 4) small = set_bias();
                 if (small) second(Small{});
                 else second(Any{});
             }
@@ -572,6 +640,22 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     wait_dma<0>();
 
     // ---- results: D[4 c + v][li] of tile (i, j) is x row 16 i + 4 c + v, W row 16 j + li.
+    // R = 4: it is x row 4 i + v over the groups of lane group c.
+    if constexpr (R == 4) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    float t = acc[i][j][v];
+                    t += __shfl_xor(t, 16);
+                    t += __shfl_xor(t, 32);
+                    acc[i][j][v] = t;
+                }
+    }
+    auto out_row = [&](int i, int v) { return R == 16 ? 16 * i + 4 * c + v : 4 * i + v; };
+    auto mine = [&](int v) { return R == 16 || v == c; };
     typedef __attribute__((address_space(3))) float lds_f32;
     if constexpr (KW > 1) {
         block_barrier();
@@ -596,8 +680,8 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                     float t = 0.0f;
 #pragma unroll
                     for (int w = 0; w < KW; ++w) t += red[(((w * NW + wn) * TM + i) * TN + j) * 256 + v * 64 + lane];
-                    const int mr = 16 * i + 4 * c + v;
-                    if (mr < mrows && col < a.n) gbl(a.y)[(m0 + mr) * a.n + col] = __half_as_ushort(__float2half_rn(t));
+                    const int mr = out_row(i, v);
+                    if (mine(v) && mr < mrows && col < a.n) gbl(a.y)[(m0 + mr) * a.n + col] = __half_as_ushort(__float2half_rn(t));
                 }
             }
         }
@@ -610,8 +694,8 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 if (col >= a.n) continue;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int mr = 16 * i + 4 * c + v;
-                    if (mr < mrows) gbl(a.y)[(m0 + mr) * a.n + col] = __half_as_ushort(__float2half_rn(acc[i][j][v]));
+                    const int mr = out_row(i, v);
+                    if (mine(v) && mr < mrows) gbl(a.y)[(m0 + mr) * a.n + col] = __half_as_ushort(__float2half_rn(acc[i][j][v]));
                 }
             }
         }
@@ -641,28 +725,28 @@ __device__ __forceinline__ int xcd_run(int b, int blocks) {
 }
 
 // One linear.
-template <typename C, int TM, int TN, int NW, int KW, int XK, int CK, int W>
+template <typename C, int TM, int TN, int NW, int KW, int XK, int CK, int W, int R>
 __device__ __forceinline__ void run_tile(const GemmArgs& a, int b, int blocks_m, lds_u8* lds) {
     const int blocks_n = (int)((a.n + C::kRowsN - 1) / C::kRowsN);
     int bn = b, bm = 0;
     if (blocks_m > 1) tile_of(b, blocks_n, blocks_m, bn, bm);
-    gemm_block<TM, TN, NW, KW, XK, CK, W>(a, (int64_t)bn * C::kRowsN, (int64_t)bm * C::kRowsM, blocks_m > 1 ? 0 : bn,
+    gemm_block<TM, TN, NW, KW, XK, CK, W, R>(a, (int64_t)bn * C::kRowsN, (int64_t)bm * C::kRowsM, blocks_m > 1 ? 0 : bn,
                                           lds);
 }
 
-template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int OCC>
+template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R, int OCC>
 __global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_kernel(const GemmArgs a, int blocks_m) {
-    using C = Cfg<TM, TN, NW, KW, XK, CK, W>;
+    using C = Cfg<TM, TN, NW, KW, XK, CK, W, R>;
     __shared__ __align__(16) uint8_t s_lds[C::LdsBytes];
     const int b = blocks_m > 1 ? xcd_run(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-    run_tile<C, TM, TN, NW, KW, XK, CK, W>(a, b, blocks_m, (lds_u8*)s_lds);
+    run_tile<C, TM, TN, NW, KW, XK, CK, W, R>(a, b, blocks_m, (lds_u8*)s_lds);
 }
 
 // Independent linears of one launch, found by binary search over their first
 // blocks: from a plan in device memory (M <= 64) ...
-template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int OCC>
+template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R, int OCC>
 __global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_plan_kernel(const DecodeEntry* __restrict__ entries, int count, int m) {
-    using C = Cfg<TM, TN, NW, KW, XK, CK, W>;
+    using C = Cfg<TM, TN, NW, KW, XK, CK, W, R>;
     __shared__ __align__(16) uint8_t s_lds[C::LdsBytes];
     const int64_t b = blockIdx.x;
     int lo = 0, hi = count - 1;
@@ -674,7 +758,7 @@ __global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_plan_kernel(const Dec
     const DecodeEntry& e = entries[lo];
     const GemmArgs a{e.packed, e.scales, e.x, e.y, e.n, e.ng, m};
     const int blocks_m = (m + C::kRowsM - 1) / C::kRowsM;
-    run_tile<C, TM, TN, NW, KW, XK, CK, W>(a, (int)(b - e.first_step), blocks_m, (lds_u8*)s_lds);
+    run_tile<C, TM, TN, NW, KW, XK, CK, W, R>(a, (int)(b - e.first_step), blocks_m, (lds_u8*)s_lds);
 }
 
 // ... or from the launch's own arguments (prompts: no plan to keep).
@@ -695,9 +779,9 @@ struct GemmList {
 };
 static_assert(sizeof(GemmList) <= 3600, "launch arguments stay below 4 KiB");
 
-template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int OCC>
+template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R, int OCC>
 __global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_list_kernel(const GemmList l) {
-    using C = Cfg<TM, TN, NW, KW, XK, CK, W>;
+    using C = Cfg<TM, TN, NW, KW, XK, CK, W, R>;
     __shared__ __align__(16) uint8_t s_lds[C::LdsBytes];
     const int b = blockIdx.x;
     int lo = 0, hi = l.count - 1;
@@ -712,41 +796,50 @@ __global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_list_kernel(const Gem
     const int blocks = (int)((a.n + C::kRowsN - 1) / C::kRowsN) * blocks_m;
     const int r = b - l.e[lo].first_block;
     if (r >= blocks) return;
-    run_tile<C, TM, TN, NW, KW, XK, CK, W>(a, xcd_run(r, blocks), blocks_m, (lds_u8*)s_lds);
+    run_tile<C, TM, TN, NW, KW, XK, CK, W, R>(a, xcd_run(r, blocks), blocks_m, (lds_u8*)s_lds);
 }
 
 // ------------------------------------------------------------- dispatch
 
-// The compiled block shapes: TM, TN, NW, KW, XK, CK, W and blocks per CU
-// that the registers are compiled for.
+// The compiled block shapes: TM, TN, NW, KW, XK, CK, W, R and blocks per CU
+// that the registers are compiled for.  16 rows of W with K over eight waves
+// are for few rows of deep K: 4096 x 14336 at M = 8 17.2 -> 12.1 us, 3072 x
+// 8192 10.8 -> 8.1.
 #define WQ_GEMM_CONFIGS(X)        \
-    X(1, 2, 4, 1, 128, 256, 4, 4) \
-    X(1, 2, 4, 2, 128, 256, 2, 2) \
-    X(1, 2, 2, 4, 128, 256, 2, 2) \
-    X(1, 2, 1, 8, 128, 256, 2, 1) \
-    X(1, 1, 1, 4, 128, 256, 2, 2) \
-    X(2, 2, 8, 1, 128, 256, 4, 2) \
-    X(2, 4, 2, 2, 128, 256, 2, 2) \
-    X(2, 2, 2, 2, 128, 256, 2, 2) \
-    X(2, 4, 1, 4, 128, 256, 2, 1) \
-    X(2, 2, 1, 4, 64, 64, 2, 2)   \
-    X(2, 1, 1, 4, 128, 256, 2, 1) \
-    X(3, 4, 4, 1, 128, 256, 2, 2) \
-    X(3, 2, 2, 2, 128, 256, 2, 2) \
-    X(3, 2, 1, 4, 128, 256, 2, 1) \
-    X(3, 1, 1, 4, 128, 256, 2, 1) \
-    X(4, 2, 8, 1, 128, 256, 2, 2) \
-    X(4, 2, 4, 1, 64, 64, 2, 4)   \
-    X(4, 4, 2, 2, 128, 256, 2, 1) \
-    X(4, 2, 2, 2, 64, 64, 2, 2)   \
-    X(4, 2, 1, 4, 64, 64, 2, 1)   \
-    X(6, 4, 4, 1, 64, 64, 2, 2)   \
-    X(8, 4, 4, 1, 64, 64, 2, 2)   \
-    X(8, 4, 8, 1, 64, 64, 2, 1)   \
-    X(8, 2, 2, 2, 64, 64, 2, 1)
+    X(1, 2, 4, 1, 128, 256, 4, 16, 4) \
+    X(1, 2, 4, 2, 128, 256, 2, 16, 2) \
+    X(1, 2, 2, 4, 128, 256, 2, 16, 2) \
+    X(1, 2, 1, 8, 128, 256, 2, 16, 1) \
+    X(1, 1, 1, 4, 128, 256, 2, 16, 2) \
+    X(2, 2, 8, 1, 128, 256, 4, 16, 2) \
+    X(2, 4, 2, 2, 128, 256, 2, 16, 2) \
+    X(2, 2, 2, 2, 128, 256, 2, 16, 2) \
+    X(2, 4, 1, 4, 128, 256, 2, 16, 1) \
+    X(2, 2, 1, 4, 64, 64, 2, 16, 2)   \
+    X(2, 1, 1, 4, 128, 256, 2, 16, 1) \
+    X(3, 4, 4, 1, 128, 256, 2, 16, 2) \
+    X(3, 2, 2, 2, 128, 256, 2, 16, 2) \
+    X(3, 2, 1, 4, 128, 256, 2, 16, 1) \
+    X(3, 1, 1, 4, 128, 256, 2, 16, 1) \
+    X(4, 2, 8, 1, 128, 256, 2, 16, 2) \
+    X(4, 2, 4, 1, 64, 64, 2, 16, 4)   \
+    X(4, 4, 2, 2, 128, 256, 2, 16, 1) \
+    X(4, 2, 2, 2, 64, 64, 2, 16, 2)   \
+    X(4, 2, 1, 4, 64, 64, 2, 16, 1)   \
+    X(6, 4, 4, 1, 64, 64, 2, 16, 2)   \
+    X(8, 4, 4, 1, 64, 64, 2, 16, 2)   \
+    X(8, 4, 8, 1, 64, 64, 2, 16, 1)   \
+    X(8, 2, 2, 2, 64, 64, 2, 16, 1)   \
+    X(1, 2, 4, 1, 128, 256, 4, 4, 4) \
+    X(1, 2, 4, 2, 128, 256, 2, 4, 2) \
+    X(1, 2, 2, 4, 128, 256, 2, 4, 2) \
+    X(1, 2, 1, 8, 128, 256, 2, 4, 1) \
+    X(1, 1, 1, 4, 128, 256, 2, 4, 2) \
+    X(1, 1, 1, 8, 128, 256, 2, 4, 1) \
+    X(1, 1, 1, 8, 128, 256, 2, 16, 1)
 
 struct Config {
-    int tm, tn, nw, kw, xk, ck;
+    int tm, tn, nw, kw, xk, ck, r;
     int occ;  // blocks per CU
     int rows_m, rows_n;
     hipError_t (*one)(const GemmArgs&, int64_t, int, hipStream_t);
@@ -754,38 +847,38 @@ struct Config {
     hipError_t (*list)(const GemmList&, int64_t, hipStream_t);
 };
 
-template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int OCC>
+template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R, int OCC>
 hipError_t launch_one(const GemmArgs& a, int64_t blocks, int blocks_m, hipStream_t stream) {
-    hipLaunchKernelGGL((gemm_kernel<TM, TN, NW, KW, XK, CK, W, OCC>), dim3((unsigned)blocks), dim3(NW * KW * kWave), 0, stream, a, blocks_m);
+    hipLaunchKernelGGL((gemm_kernel<TM, TN, NW, KW, XK, CK, W, R, OCC>), dim3((unsigned)blocks), dim3(NW * KW * kWave), 0, stream, a, blocks_m);
     return hipGetLastError();
 }
-template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int OCC>
+template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R, int OCC>
 hipError_t launch_plan(const DecodeEntry* entries, int count, int64_t blocks, int m, hipStream_t stream) {
     if constexpr (TM <= 4) {
-        hipLaunchKernelGGL((gemm_plan_kernel<TM, TN, NW, KW, XK, CK, W, OCC>), dim3((unsigned)blocks), dim3(NW * KW * kWave), 0, stream, entries, count, m);
+        hipLaunchKernelGGL((gemm_plan_kernel<TM, TN, NW, KW, XK, CK, W, R, OCC>), dim3((unsigned)blocks), dim3(NW * KW * kWave), 0, stream, entries, count, m);
         return hipGetLastError();
     } else {
         return hipErrorInvalidValue;  // plans are made for M <= 64 only
     }
 }
-template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int OCC>
+template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R, int OCC>
 hipError_t launch_list(const GemmList& l, int64_t blocks, hipStream_t stream) {
-    if constexpr (TM >= 2) {
-        hipLaunchKernelGGL((gemm_list_kernel<TM, TN, NW, KW, XK, CK, W, OCC>), dim3((unsigned)blocks), dim3(NW * KW * kWave), 0, stream, l);
+    if constexpr (TM >= 2 && R == 16) {
+        hipLaunchKernelGGL((gemm_list_kernel<TM, TN, NW, KW, XK, CK, W, R, OCC>), dim3((unsigned)blocks), dim3(NW * KW * kWave), 0, stream, l);
         return hipGetLastError();
     } else {
         return hipErrorInvalidValue;  // lists are made for M > 64 only
     }
 }
 
-template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int OCC>
+template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R, int OCC>
 constexpr Config config_of() {
-    using C = Cfg<TM, TN, NW, KW, XK, CK, W>;
+    using C = Cfg<TM, TN, NW, KW, XK, CK, W, R>;
     static_assert(C::LdsBytes <= 160 * 1024, "a block fits one CU");
     const int by_lds = 160 * 1024 / C::LdsBytes;
-    return Config{TM, TN, NW, KW, XK, CK, by_lds < OCC ? by_lds : OCC, C::kRowsM, C::kRowsN,
-                  launch_one<TM, TN, NW, KW, XK, CK, W, OCC>, launch_plan<TM, TN, NW, KW, XK, CK, W, OCC>,
-                  launch_list<TM, TN, NW, KW, XK, CK, W, OCC>};
+    return Config{TM, TN, NW, KW, XK, CK, R, by_lds < OCC ? by_lds : OCC, C::kRowsM, C::kRowsN,
+                  launch_one<TM, TN, NW, KW, XK, CK, W, R, OCC>, launch_plan<TM, TN, NW, KW, XK, CK, W, R, OCC>,
+                  launch_list<TM, TN, NW, KW, XK, CK, W, R, OCC>};
 }
 
 #define WQ_GEMM_ROW(...) config_of<__VA_ARGS__>(),
@@ -807,7 +900,7 @@ double block_us(const Config& c, int64_t k, int resident) {
     const double valu = (c.ck == kStageK ? 12 : 16) * 4.0 * 1.73, mfma = 16.0 * c.tm * 1.62;
     const double cycles =
         pieces * (per_simd <= 1.0 ? valu + mfma : std::max(valu, mfma) + 0.26 * std::min(valu, mfma));
-    const double bytes = c.kw * c.rows_m * c.xk * 2.0 + waves * 16 * c.tn * c.xk * 0.5625;
+    const double bytes = c.kw * 16 * c.tm * c.xk * 2.0 + waves * 16 * c.tn * c.xk * 0.5625;
     const double stages = std::ceil((double)k / (c.xk * c.kw));
     return 2.9 + stages * (0.06 + resident * bytes / 168e3 + per_simd * cycles / 2300.0);
 }
@@ -849,17 +942,19 @@ double launch_us(const Config& c, const Shape* lin, int count, int64_t m) {
 }
 
 bool config_allowed(const Config& c, int64_t m) {
-    // One pass over W up to 64 rows, with the lowest tile that holds them;
+    // R = 4 up to four rows: the times of 16 rows (single linears within 3%, 3B
+    // step at M = 4 289-293 against 291 us) with scales in fp32.  One pass over W up to 64 rows, with the lowest tile that holds them;
     // from there on tiles of at least 32 rows (48 rows, and 64 x 256 in whole
     // lines, were never the fastest).
-    if (m <= 64) return c.rows_m >= m && c.rows_m < m + 16;
-    return c.tm >= 2 && c.tm != 3 && !(c.tm == 4 && c.rows_n == 256);
+    if (m <= 4) return c.r == 4;
+    if (m <= 64) return c.r == 16 && c.rows_m >= m && c.rows_m < m + 16;
+    return c.r == 16 && c.tm >= 2 && c.tm != 3 && !(c.tm == 4 && c.rows_n == 256);
 }
 
 int pick_config(const Shape* lin, int count, int64_t m) {
     if (const char* e = std::getenv("WQ_GEMM_CONFIG")) {
         const int i = std::atoi(e);
-        if (i >= 0 && i < kConfigCount && (m > 64 ? kConfigs[i].tm >= 2 : kConfigs[i].tm <= 4)) return i;
+        if (i >= 0 && i < kConfigCount && (m > 64 ? kConfigs[i].tm >= 2 && kConfigs[i].r == 16 : kConfigs[i].tm <= 4)) return i;
     }
     int best = -1;
     double best_us = 0.0;

@@ -27,11 +27,10 @@ hipError_t launch_gemv(const uint32_t* packed, const uint16_t* scales,
                        const uint16_t* x, uint16_t* y,
                        int64_t n, int64_t k, int64_t m, hipStream_t stream);
 
-// Smallest batch that uses the matrix cores; M = 2 runs on the vector ALUs.
-// Measured on the 3B- and 8B-class decode steps: the matrix cores are faster
-// from M = 3 on (3B step at M = 4: 435 against 475 us; 8B step at M = 7: 930
-// against 1624 us), the vector kernel at M = 2 (395 against 479 us).
-constexpr int kMatrixCoreMinM = 3;
+// Smallest batch that uses the matrix cores.  At M = 2, vector kernel against
+// GEMM: 3B-class step 342 against 282 us, 8B-class step 778 against 631,
+// 128256 x 3072 67.9 against 38.8 (few rows of deep K: launch_gemv).
+constexpr int kMatrixCoreMinM = 2;
 
 // Largest batch of the planned decode steps (and of the vector kernel);
 // larger ones (prompts) keep no plan.

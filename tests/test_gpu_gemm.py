@@ -103,3 +103,55 @@ def test_prompt_list_of_many_linears_exact():
     torch.cuda.synchronize()
     for (_, _, _, y), ref in zip(lins, refs):
         assert np.array_equal(to_host(y, np.uint16), ref.view(np.uint16))
+
+
+# Blocks that hold four rows of x per tile, each in the places of four lane
+# groups, so that a tile's sums are those of single groups.
+GROUP_CONFIGS = range(24, 31)  # the last one is the 16-row shape with K over eight waves
+
+
+@pytest.mark.parametrize("m", [2, 3, 4, 5, 8, 19])
+@pytest.mark.parametrize("config", GROUP_CONFIGS)
+def test_group_sum_shape_exact(config, m, monkeypatch):
+    """Ragged rows in one block, or several blocks of rows; K of four whole
+    stages and one group."""
+    monkeypatch.setenv("WQ_GEMM_CONFIG", str(config))
+    announce(f"gemm config {config} M={m} N=275 K=1056")
+    _check(m, 275, 1056, 100 * config + m, shift=m % 2)
+
+
+@pytest.mark.parametrize("m,n,k", [(2, 1, 32), (2, 17, 64), (4, 33, 2080), (5, 257, 96), (8, 65, 8224), (7, 31, 224),
+                                   (2, 300, 16384), (8, 1000, 8192)])
+def test_group_sum_picked_exact(m, n, k):
+    announce(f"gemm M={m} N={n} K={k}")
+    if k > 8224:  # keep every sum exact: at most 4 * 8 * 2^-4 * 16384 = 2^15
+        packed, scales, x, sd = _case(m, n, k, m + n, 1, -10, -4)
+        y = to_host(gpu_gemv(to_dev(packed), sd, to_dev(x)), np.uint16)
+        assert np.array_equal(y, oracle.gemv(packed, scales, x, n, k).view(np.uint16))
+    else:
+        _check(m, n, k, m + n + k, shift=n % 2)
+
+
+@pytest.mark.parametrize("m", [2, 4, 7])
+def test_group_sum_special_values(m):
+    """An infinity in x gives what the sum of its products gives (infinite,
+    or no number at a weight of zero), the largest x stays finite, and other
+    rows keep their bits."""
+    n, k = 70, 352
+    packed, scales, x, _ = _case(m, n, k, 9 * m)
+    ref = oracle.gemv(packed, scales, x, n, k).view(np.uint16)
+    w = oracle.dequant(packed, scales, n, k)
+    xb = x.copy()
+    xb[1, 300] = np.inf
+    announce(f"gemm infinity M={m}")
+    y = to_host(gpu_gemv(to_dev(packed), to_dev(scales), to_dev(xb)), np.uint16)
+    keep = np.arange(m) != 1
+    assert np.array_equal(y[keep], ref[keep])
+    with np.errstate(invalid="ignore"):
+        want = np.inf * w[:, 300]
+    assert np.array_equal(y[1].view(np.float16).astype(np.float64), want, equal_nan=True)
+    xb = np.zeros_like(x)
+    xb[1, ::32] = 65504.0
+    s = np.full_like(scales, 0x0001)  # 2^-24
+    y = to_host(gpu_gemv(to_dev(packed), to_dev(s), to_dev(xb)), np.uint16)
+    assert np.array_equal(y, oracle.gemv(packed, s, xb, n, k).view(np.uint16))
