@@ -12,12 +12,16 @@
 // Up to four rows of x (R = 4) a 16-row tile holds each row four times, once
 // for each lane group's words and zero elsewhere, so that after the four words
 // a tile's sums are those of single groups, in the lane that holds the group's
-// scale.  The codes then go to the matrix cores as they are (q 2^-20, exact
-// subnormals: 7 operations per word), starting from -8 2^-20 times the sums
-// of x, and the scale is applied in fp32.  Before, M = 2 ran on the vector
-// kernel (fp32 scales as well); 3B-class step at M = 2 342 -> 282 us, 8B-class
-// 778 -> 631, at M = 4 370 -> 293 and 831 -> 653 (against the step's earlier
-// kernel).  From M = 5 on two such tiles were 15-24% slower than one of 16.
+// scale.  The codes go to the matrix cores as (q - 8) 2^-20, exact subnormals
+// (11 operations per word), and the scale is applied in fp32.  (Raw codes,
+// with the sums started from -8 times those of x, take 7 operations, but their
+// rounding error grows with |x| where q = 8: activations of 1e3 to 6e4 at zero
+// weights put results outside the documented bound.  Exact codes cost 4% on
+// 28672 x 4096, 14.5 -> 15.15 us, and under 0.5% on the steps.)  Before, M = 2
+// ran on the vector kernel (fp32 scales as well); 3B-class step at M = 2 345 ->
+// 279 us, 8B-class 787 -> 624, at M = 4 369 -> 288 and 822 -> 642 (against the
+// step's earlier kernel).  From M = 5 on two such tiles were 15-24% slower than
+// one of 16.
 //
 // Loads.  Codes, scales and x all go straight into LDS (buffer loads with
 // the LDS destination, 16 bytes per lane), so the bytes in flight are bounded
@@ -152,8 +156,7 @@ __device__ __forceinline__ half8 dequant8_small(uint32_t w, half2v s20, half2v m
     return __builtin_bit_cast(half8, r);
 }
 
-// The codes alone, q 2^-20 as subnormals, or (q - 8) 2^-20; both are exact.
-template <bool CENTRED>
+// The codes without a scale: (q - 8) 2^-20, exact subnormals.
 __device__ __forceinline__ half8 codes8(uint32_t w) {
     const half2v m8 = {(_Float16)-0x1p-17f, (_Float16)-0x1p-17f};
     const uint32_t od = w & 0xF0F0F0F0u, ev = (w << 4) & 0xF0F0F0F0u;
@@ -161,7 +164,7 @@ __device__ __forceinline__ half8 codes8(uint32_t w) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const uint32_t t = __builtin_amdgcn_perm(od, ev, 0x0C000C00u | (uint32_t)((4 + j) << 16 | j));
-        r[j] = CENTRED ? __builtin_bit_cast(uint32_t, as_h2(t) + m8) : t;
+        r[j] = __builtin_bit_cast(uint32_t, as_h2(t) + m8);
     }
     return __builtin_bit_cast(half8, r);
 }
@@ -377,17 +380,16 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     };
     // Multiplies of tile tt with the part of x in `slot`; the scale is half h
     // of its pair.
-    float4v bias[TM];  // R = 4: -8 2^-20 times the sums of x over each group
     auto multiply = [&](auto small, const uint32_t* wd, const Scales& sc, int h, int slot, int tt) {
         auto both = [&](half2v v) { return half2v{v[h], v[h]}; };
         constexpr bool fast = decltype(small)::value;
         if constexpr (R == 4) {
             float4v d[TM];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) d[i] = fast ? bias[i] : float4v{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int i = 0; i < TM; ++i) d[i] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int t = 0; t < WPL; ++t) {
-                const half8 fb = codes8<!fast>(wd[t]);
+                const half8 fb = codes8(wd[t]);
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
                     d[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[slot][i][t], fb, d[i], 0, 0, 0);
@@ -408,23 +410,6 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
             for (int i = 0; i < TM; ++i)
                 acc[i][tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[slot][i][t], fb, acc[i][tt], 0, 0, 0);
         }
-    };
-    // R = 4: the bias, and whether it is finite, i.e. x holds no infinity
-    // (which times q, less itself times 8, would be no number).
-    auto set_bias = [&] {
-        const _Float16 b = (_Float16)-0x1p-17f;
-        const half8 fb = {b, b, b, b, b, b, b, b};
-        float z = 0.0f;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            bias[i] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int t = 0; t < WPL; ++t)
-                bias[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[0][i][t], fb, bias[i], 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) z = __builtin_fmaf(bias[i][v], 0.0f, z);
-        }
-        return __builtin_amdgcn_ballot_w64(z != z) == 0;
     };
     // Whether every lane's scales allow the short dequantization.
     auto all_small = [&](uint32_t mx) { return __builtin_amdgcn_ballot_w64(max(mx & 0xFFFFu, mx >> 16) >= kSmallScale) == 0; };
@@ -529,9 +514,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 issue_x(st, it < range, 1, 1);
                 load_a(0, 0, 0);
                 const uint32_t mx = read_scales(it, st);
-                bool small;
-                if constexpr (R == 4) small = set_bias();
-                else small = all_small(mx);
+                const bool small = R == 16 && all_small(mx);  // R = 4 has one form
                 auto first = [&](auto sm) {
                     // Newer than tile 0's codes: at most every other tile's and x.
                     if (it == 0) wait_dma<2 * (TN - 1) + NX>();
@@ -568,7 +551,6 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 block_sync<NW>();
                 issue_x(next, more, 0, 0);
                 load_a(1, 0, 0);
-                if constexpr (R == 4) small = set_bias();
                 if (small) second(Small{});
                 else second(Any{});
             }

@@ -155,3 +155,33 @@ def test_group_sum_special_values(m):
     s = np.full_like(scales, 0x0001)  # 2^-24
     y = to_host(gpu_gemv(to_dev(packed), to_dev(s), to_dev(xb)), np.uint16)
     assert np.array_equal(y, oracle.gemv(packed, s, xb, n, k).view(np.uint16))
+
+
+@pytest.mark.parametrize("big", [1000.0, 10000.0, 60000.0])
+@pytest.mark.parametrize("scale", [0.02, 0.2, 1.0])
+@pytest.mark.parametrize("m", [2, 3, 4])
+def test_outliers_at_zero_weights(m, scale, big):
+    """Activations of up to 6e4 in every group, where the code is 8 (weight
+    zero), among small ones: their products are exactly zero, so they add
+    nothing to the documented bound and must add nothing to the error."""
+    import torch
+
+    from paper_2412_15803_amd import wq
+
+    n, k = 70, 352
+    packed = wl.random_words_host(31 * m, n, k)
+    col = np.arange(5, k, 32)  # element 5 of its word
+    packed[:, col // 8] = (packed[:, col // 8] & ~np.uint32(0xF << 20)) | np.uint32(8 << 20)
+    scales = np.full((n, k // 32), scale, dtype=np.float16).view(np.uint16)
+    rng = np.random.default_rng(int(big) + m)
+    x = (0.01 * rng.standard_normal((m, k))).astype(np.float16)
+    x[:, col] = np.where(rng.random((m, col.size)) < 0.5, big, -big)
+    ref, bound = oracle.gemv(packed, scales, x, n, k), oracle.tol_bound(packed, scales, x, n, k)
+    announce(f"gemm outliers M={m} scale {scale} x {big}")
+    pd, sd, xd = to_dev(packed), to_dev(scales), to_dev(x)
+    y = to_host(gpu_gemv(pd, sd, xd), np.float16)
+    assert np.all(oracle.within_tolerance(y, ref, bound))
+    yd = torch.full((m, n), float("nan"), dtype=torch.float16, device="cuda:0")
+    wq.wq_decode_linears([(pd, sd, xd, yd)], m=m)
+    torch.cuda.synchronize()
+    assert np.all(oracle.within_tolerance(to_host(yd, np.float16), ref, bound))
