@@ -107,7 +107,8 @@ void split_groups(const wq_linear* lin, int count, int64_t m, Deps& reads, Deps&
     for (int i = 0; i < count; ++i) {
         const wq_linear& l = lin[i];
         const bool too_long = m == 1 && l.K / 32 > 64 * kDecodeMaxGpl;
-        const bool too_wide = m > 2 && !(m > kMaxSmallBatchM ? prefill_fits(l.N, l.K, m) : gemm_fits(l.N, l.K, m));
+        const bool too_wide = m >= kMatrixCoreMinM &&
+                              !(m > kMaxSmallBatchM ? prefill_fits(l.N, l.K, m) : gemm_fits(l.N, l.K, m));
         if (too_long || too_wide || !fits_rsrc(l.N, l.K / 32)) {
             if (i > begin) emit(Group{begin, i, true});
             emit(Group{i, i + 1, false});
@@ -171,7 +172,7 @@ struct BatchPlan {
 // wide grouped kernels.
 GroupPlan plan_group(const wq_linear* lin, const Group& g, int capacity4, int capacity8, PlanBuf& out);
 
-// Append the matrix-core (M >= 3) plan of a group at m rows.
+// Append the matrix-core (M >= kMatrixCoreMinM) plan of a group at m rows.
 BatchPlan plan_batch_group(const wq_linear* lin, const Group& g, int64_t m, PlanBuf& out);
 
 // Append the vector small-batch (M < 8) plan of a group, `target` waves.

@@ -2,6 +2,8 @@
 
   * the kernel-dispatch predicates (wq_limits.h) at the 32-bit buffer-offset
     boundaries, in a small C++ program built with g++ and ASan/UBSan;
+  * the splitting of a descriptor list into launches (wq_plan.h) at the same
+    boundaries, likewise;
   * the whole C-ABI validation suite (tests/test_abi.py) against a build of
     the library whose host code carries AddressSanitizer: argument checks,
     span bookkeeping and the error paths run instrumented.
@@ -25,6 +27,19 @@ def test_dispatch_predicates_at_offset_limits(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=address,undefined",
                     "-fno-sanitize-recover=all", "-I", CSRC, os.path.join(HERE, "host", "limits_test.cpp"),
                     "-o", exe], check=True, capture_output=True, text=True)
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert out.stdout.strip() == "ok"
+
+
+@pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
+                    reason="needs g++ and the HIP headers")
+def test_descriptor_lists_split_into_launches(tmp_path):
+    exe = str(tmp_path / "plan_test")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=address,undefined",
+                    "-fno-sanitize-recover=all", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I", CSRC,
+                    "-I", os.path.join(ROOT, "include"), os.path.join(HERE, "host", "plan_test.cpp"), "-o", exe],
+                   check=True, capture_output=True, text=True)
     out = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0, out.stdout + out.stderr
     assert out.stdout.strip() == "ok"
