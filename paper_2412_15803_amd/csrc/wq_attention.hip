@@ -536,16 +536,20 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(const Params p) {
     // Chunk c of the head lies `step` slots after chunk c - 1; at most `most` of them.
     int64_t base_slot = head * p.splits, step = 1;
     int most = p.splits, have = 0;
+    const int len = p.lens[s];
+    const bool empty = bad_length(p, len) || len == 0;
     if constexpr (BY_LENGTH) {
+        // The row still holds its units only where the sequence has any:
+        // otherwise wave 0 writes the result below while another wave may not
+        // have read the row yet, and what was read is not used.
         const int2 info = *reinterpret_cast<const int2*>(o);
-        base_slot = (int64_t)info.x * p.hq + head % p.hq;
+        base_slot = empty ? 0 : (int64_t)info.x * p.hq + head % p.hq;
         step = p.hq;
-        most = have = info.y;
+        most = have = empty ? 0 : info.y;
     }
     const float2* ml = p.part_ml + base_slot;
     const float4* pa = reinterpret_cast<const float4*>(p.part_acc + base_slot * kD) + cq;
 
-    const int len = p.lens[s];
     float m = -INFINITY, l = 0.0f;
     float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     int n = most;  // chunks that hold data; known once the length arrives
@@ -559,7 +563,7 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(const Params p) {
             v[j] = pa[c * kCols];
         }
         if (base == slot) {
-            if (bad_length(p, len) || len == 0) break;
+            if (empty) break;
             n = have ? have : (len + p.chunk - 1) / p.chunk;
         }
         float mx = m;
@@ -585,7 +589,7 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(const Params p) {
         }
         m = mx;
     }
-    if (bad_length(p, len) || len == 0) {
+    if (empty) {
         if (tid < kD) o[tid] = len == 0 ? 0 : kHalfNaN;
         return;
     }

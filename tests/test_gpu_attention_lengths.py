@@ -54,6 +54,24 @@ def test_lengths_invalid_sequences_stay_apart():
     check_tolerance(attn_cases.select_sequences(case, keep), got[keep], "valid sequences")
 
 
+@pytest.mark.parametrize("hq,hkv", [(24, 8), (8, 1)])
+def test_lengths_many_invalid_sequences(hq, hkv):
+    """Two thirds of the sequences have a bad or an empty length, so their
+    merges write at once, without a unit to read: NaN or zeros in every
+    element, and the others within the tolerance."""
+    lens = tuple(0 if i % 3 == 1 else 700 + 97 * i for i in range(48))
+    announce(f"attention by length, many invalid sequences hq={hq}")
+    case = attn_cases.random_case(72 + hq, hq, hkv, 128, 16, lens, extra_pages=2, max_pages=600)
+    bad_lens = case.seq_lens.copy()
+    bad = np.arange(len(lens)) % 3 == 2
+    bad_lens[bad] = np.where(np.arange(bad.sum()) % 2, -1, 8193)
+    got = gpu_attention(case._replace(seq_lens=bad_lens), max_seq_len=8192)
+    assert np.all(np.isnan(got[bad].astype(np.float32)))
+    assert np.all(got[np.asarray(lens) == 0] == 0)
+    keep = [i for i in range(len(lens)) if i % 3 == 0]
+    check_tolerance(attn_cases.select_sequences(case, keep), got[keep], "valid sequences")
+
+
 def test_whole_short_sequences_need_no_workspace():
     """Up to 192 tokens one workgroup takes a sequence whole."""
     from paper_2412_15803_amd import wq
