@@ -40,6 +40,7 @@
 #include <cstdlib>
 
 #include "wq_attention.h"
+#include "wq_attn_plan.h"
 #include "wq_device.h"
 #include "wq_internal.h"
 
@@ -58,8 +59,7 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kRowsPerLoad = 4;                              // tokens per wave-wide load
 constexpr int kLoadsPerBlock = 4;
 constexpr int kBlockTokens = kRowsPerLoad * kLoadsPerBlock;  // 16 tokens of one wave
-constexpr int kChunkQuantum = kWaves * kBlockTokens;        // 64 tokens: a block per wave
-constexpr int kMaxChunk = 4096;
+static_assert(kChunkQuantum == kWaves * kBlockTokens, "a block per wave");
 constexpr int kMaxSplits = 1024;
 static_assert(WQ_ATTN_MAX_SEQ_LEN / kMaxChunk <= kMaxSplits, "chunks per sequence stay bounded");
 constexpr uint16_t kHalfNaN = 0x7E00;
@@ -76,8 +76,8 @@ struct Params {
     const int32_t* table;
     const int32_t* lens;
     uint16_t* out;
-    float* part_acc;    // [seq * hq + h][splits][kD]
-    float2* part_ml;    // [seq * hq + h][splits]: (m, l)
+    float* part_acc;    // [seq * hq + h][splits][kD]; by the lengths [unit][hq][kD]
+    float2* part_ml;    // [seq * hq + h][splits], [unit][hq]: (m, l)
     int64_t max_pages;  // row length of the block table
     uint32_t page_stride;  // elements per page: hkv * page_size * kD
     int32_t num_pages;
@@ -187,9 +187,7 @@ __device__ __forceinline__ void fold_pair(State& st) {
 // of 64) that cuts all sequences into at most `units` chunks per kv head, the
 // number that the workspace has room for.  Unit u is then a chunk of one
 // sequence, the sequences in order, each cut into equal chunks.
-constexpr int kMaxSeqsByLength = 1024;
 constexpr int kCandidates = 16;
-constexpr int kMinUnitChunk = 256;  // tokens
 
 struct Unit {
     int seq, len, chunk, first, count;  // sequence, its length, chunk of it; its first unit and number of units
@@ -617,15 +615,6 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(const Params p) {
 
 // ------------------------------------------------------------------- host
 
-struct Plan {
-    int64_t chunk;
-    int64_t splits;
-    int64_t units;     // nonzero: chunks by the lengths, at most this many per kv head
-    int64_t max_chunk; // tokens of the longest chunk
-    size_t ml_offset;  // bytes of part_acc
-    size_t ws_bytes;
-};
-
 bool xcd_placement() {
     const char* e = getenv("WQ_ATTN_XCD_LOCAL");
     return !e || strtol(e, nullptr, 10) != 0;
@@ -637,46 +626,21 @@ int64_t target_blocks() {
     return v > 0 ? v : 512;
 }
 
-constexpr int64_t kMaxWhole = 192;
-constexpr int64_t kByLengthChunk = 512;
-
 bool by_length() {
     const char* e = getenv("WQ_ATTN_BY_LENGTH");
     return !e || strtol(e, nullptr, 10) != 0;
 }
 
-// Chunk length: a multiple of 64 tokens that gives the split launch about
-// target_blocks() workgroups (what the chip holds at once, so there is a
-// single round of them), at most kMaxChunk tokens; with sequences of at most
-// WQ_ATTN_MAX_SEQ_LEN tokens that keeps a sequence within kMaxSplits chunks.
-Plan make_plan(int64_t seqs, int64_t hq, int64_t hkv, int64_t max_seq_len) {
-    const int64_t len = std::max<int64_t>(max_seq_len, 1);
-    const int64_t want = std::max<int64_t>(1, target_blocks() / (seqs * hkv));  // chunks per sequence
-    int64_t chunk = (len + want - 1) / want;
-    chunk = (chunk + kChunkQuantum - 1) / kChunkQuantum * kChunkQuantum;
-    chunk = std::min<int64_t>(std::max<int64_t>(chunk, kChunkQuantum), kMaxChunk);
-    // One workgroup takes a short sequence whole: the second launch would cost
-    // more than it saves (24 / 8 heads, one sequence: 192 tokens 6.3 us against
-    // 7.2 us, 256 tokens 7.9 against 7.4).
-    if (len <= kMaxWhole) chunk = (len + kChunkQuantum - 1) / kChunkQuantum * kChunkQuantum;
-    Plan pl{chunk, (len + chunk - 1) / chunk, 0, chunk, 0, 0};
-    // Several sequences in chunks of at least kByLengthChunk tokens: chunks
-    // follow the lengths (which costs two more round trips), in the same
-    // workspace.
-    if (seqs > 1 && seqs <= kMaxSeqsByLength && seqs * len <= INT32_MAX / 2 && pl.splits > 1 && chunk >= kByLengthChunk &&
-        by_length()) {
-        pl.units = seqs * pl.splits;
-        // Six query heads or more take over 256 registers: one workgroup per
-        // CU, so no more of them than CUs while that cuts every sequence.
-        if (hq / hkv >= 6) pl.units = std::min(pl.units, std::max(2 * seqs, 256 / hkv));
-        const int64_t hi = (seqs * len + pl.units - seqs - 1) / (pl.units - seqs);
-        pl.max_chunk = (std::max<int64_t>(hi, kMinUnitChunk) + 63) / 64 * 64;
-    }
-    if (pl.splits > 1) {
-        pl.ml_offset = (size_t)(seqs * hq * pl.splits * kD * 4);
-        pl.ws_bytes = pl.ml_offset + (size_t)(seqs * hq * pl.splits * 8);
-    }
-    return pl;
+Plan plan_of(int64_t seqs, int64_t hq, int64_t hkv, int64_t max_seq_len, int64_t page_size) {
+    return make_plan(seqs, hq, hkv, max_seq_len, page_size, target_blocks(), by_length());
+}
+
+// The workspace: part_acc, then part_ml from byte acc_bytes on.
+size_t acc_bytes(const Plan& pl, int64_t seqs, int64_t hq) {
+    return pl.splits > 1 ? (size_t)(seqs * hq * pl.splits * kD * 4) : 0;
+}
+size_t workspace_bytes_of(const Plan& pl, int64_t seqs, int64_t hq) {
+    return pl.splits > 1 ? acc_bytes(pl, seqs, hq) + (size_t)(seqs * hq * pl.splits * 8) : 0;
 }
 
 template <int G>
@@ -757,7 +721,7 @@ wq_status check_sizes(const char* fn, int64_t seqs, int64_t hq, int64_t hkv, int
     if (max_seq_len < 0 || max_seq_len > WQ_ATTN_MAX_SEQ_LEN)
         return err(WQ_ERR_INVALID_ARG, "%s: max_seq_len must be in [0, %lld] (got %lld)", fn,
                    (long long)WQ_ATTN_MAX_SEQ_LEN, (long long)max_seq_len);
-    const Plan pl = make_plan(seqs, hq, hkv, max_seq_len);
+    const Plan pl = plan_of(seqs, hq, hkv, max_seq_len, 1);
     if (seqs * hkv * pl.splits > INT32_MAX || seqs * hq > INT32_MAX)
         return err(WQ_ERR_INVALID_ARG, "%s: too many workgroups for one launch", fn);
     return WQ_OK;
@@ -777,7 +741,7 @@ wq_status wq_paged_attention_workspace_size(int64_t num_seqs, int64_t num_q_head
     if (!bytes) return err(WQ_ERR_INVALID_ARG, "%s: null output pointer", fn);
     const wq_status st = check_sizes(fn, num_seqs, num_q_heads, num_kv_heads, head_dim, max_seq_len);
     if (st != WQ_OK) return st;
-    *bytes = make_plan(num_seqs, num_q_heads, num_kv_heads, max_seq_len).ws_bytes;
+    *bytes = workspace_bytes_of(plan_of(num_seqs, num_q_heads, num_kv_heads, max_seq_len, 1), num_seqs, num_q_heads);
     return WQ_OK;
 }
 
@@ -809,18 +773,19 @@ wq_status wq_paged_attention(const uint16_t* q, const uint16_t* k_cache, const u
     if (!aligned(block_table, 4) || !aligned(seq_lens, 4))
         return err(WQ_ERR_MISALIGNED, "%s: block_table and seq_lens must be 4-byte aligned", fn);
 
-    const Plan pl = make_plan(num_seqs, num_q_heads, num_kv_heads, max_seq_len);
-    if (pl.ws_bytes > 0) {
-        if (!workspace) return err(WQ_ERR_INVALID_ARG, "%s: a workspace of %zu bytes is needed", fn, pl.ws_bytes);
-        if (workspace_bytes < pl.ws_bytes)
+    const Plan pl = plan_of(num_seqs, num_q_heads, num_kv_heads, max_seq_len, page_size);
+    const size_t ws_bytes = workspace_bytes_of(pl, num_seqs, num_q_heads);
+    if (ws_bytes > 0) {
+        if (!workspace) return err(WQ_ERR_INVALID_ARG, "%s: a workspace of %zu bytes is needed", fn, ws_bytes);
+        if (workspace_bytes < ws_bytes)
             return err(WQ_ERR_INVALID_ARG, "%s: workspace of %zu bytes is below the %zu needed", fn, workspace_bytes,
-                       pl.ws_bytes);
+                       ws_bytes);
         if (!aligned(workspace, 16)) return err(WQ_ERR_MISALIGNED, "%s: workspace must be 16-byte aligned", fn);
     }
     const uint64_t qo_bytes = (uint64_t)num_seqs * num_q_heads * head_dim * 2;
     const uint64_t cache_bytes = (uint64_t)num_pages * num_kv_heads * page_size * head_dim * 2;
     const Span so = span(out, qo_bytes);
-    const Span sw = span(workspace, pl.ws_bytes);
+    const Span sw = span(workspace, ws_bytes);
     const Span inputs[] = {span(q, qo_bytes), span(k_cache, cache_bytes), span(v_cache, cache_bytes),
                            span(block_table, (uint64_t)num_seqs * max_pages_per_seq * 4),
                            span(seq_lens, (uint64_t)num_seqs * 4)};
@@ -832,8 +797,7 @@ wq_status wq_paged_attention(const uint16_t* q, const uint16_t* k_cache, const u
 
     const int group = (int)(num_q_heads / num_kv_heads);
     const int log2_page = log2_of(page_size);
-    // Pages a chunk can touch: it may start inside a page.
-    const int64_t pages_per_chunk = (pl.max_chunk >> log2_page) + 2;
+    const int64_t pages_per_chunk = chunk_pages(pl, page_size);
 
     Params p{};
     p.q = q;
@@ -842,8 +806,8 @@ wq_status wq_paged_attention(const uint16_t* q, const uint16_t* k_cache, const u
     p.table = block_table;
     p.lens = seq_lens;
     p.out = out;
-    p.part_acc = pl.ws_bytes ? static_cast<float*>(workspace) : nullptr;
-    p.part_ml = pl.ws_bytes ? reinterpret_cast<float2*>(static_cast<char*>(workspace) + pl.ml_offset) : nullptr;
+    p.part_acc = ws_bytes ? static_cast<float*>(workspace) : nullptr;
+    p.part_ml = ws_bytes ? reinterpret_cast<float2*>(static_cast<char*>(workspace) + acc_bytes(pl, num_seqs, num_q_heads)) : nullptr;
     p.max_pages = max_pages_per_seq;
     p.page_stride = (uint32_t)(num_kv_heads * page_size * head_dim);
     p.num_pages = (int32_t)num_pages;
@@ -856,9 +820,9 @@ wq_status wq_paged_attention(const uint16_t* q, const uint16_t* k_cache, const u
     p.pages_per_chunk = (int32_t)pages_per_chunk;
     p.pages_lds = (int32_t)((pages_per_chunk * 4 + 15) / 16 * 16);
     p.c = (float)((double)scale * 1.4426950408889634);  // log2(e)
-    // Place pairs by XCD only when every XCD gets the same number of them.
     p.seqs = (int32_t)num_seqs;
     p.units = (int32_t)pl.units;
+    // Place pairs by XCD only when every XCD gets the same number of them.
     p.xcd_local = pl.splits > 1 && (num_seqs * num_kv_heads) % kXcds == 0 && xcd_placement();
 
     (void)hipGetLastError();

@@ -22,6 +22,10 @@ CASES = [
     (16, 2, 64, (1, 0, 0, 2, 0), 40000),                 # almost nothing to do under a loose bound
     (4, 4, 1, (700, 64, 65, 128, 8000), 8000),           # pages of one token
     (6, 2, 16, tuple(64 * i for i in range(1, 131)), 8320),  # 130 sequences of whole chunk quanta
+    # Six query heads or more under a long bound: the block-table entries of the longest chunk have to fit the LDS.
+    (28, 4, 1, tuple(1 + 13 * i for i in range(63)) + (20000,), 41000),
+    (64, 8, 1, tuple(5 + 29 * i for i in range(31)) + (9000,), 65536),
+    (48, 8, 16, tuple(3 + 70 * i for i in range(15)) + (17000,), 1 << 20),
 ]
 
 

@@ -4,6 +4,7 @@
     boundaries, in a small C++ program built with g++ and ASan/UBSan;
   * the splitting of a descriptor list into launches (wq_plan.h) at the same
     boundaries, likewise;
+  * the split of an attention call (wq_attn_plan.h) over the accepted ranges;
   * the whole C-ABI validation suite (tests/test_abi.py) against a build of
     the library whose host code carries AddressSanitizer: argument checks,
     span bookkeeping and the error paths run instrumented.
@@ -40,6 +41,17 @@ def test_descriptor_lists_split_into_launches(tmp_path):
                     "-fno-sanitize-recover=all", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include", "-I", CSRC,
                     "-I", os.path.join(ROOT, "include"), os.path.join(HERE, "host", "plan_test.cpp"), "-o", exe],
                    check=True, capture_output=True, text=True)
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert out.stdout.strip() == "ok"
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_attention_split_over_the_accepted_ranges(tmp_path):
+    exe = str(tmp_path / "attn_plan_test")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=address,undefined",
+                    "-fno-sanitize-recover=all", "-I", CSRC, os.path.join(HERE, "host", "attn_plan_test.cpp"),
+                    "-o", exe], check=True, capture_output=True, text=True)
     out = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0, out.stdout + out.stderr
     assert out.stdout.strip() == "ok"
