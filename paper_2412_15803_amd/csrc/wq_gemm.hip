@@ -727,20 +727,20 @@ __global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_kernel(const GemmArgs
 // Independent linears of one launch, found by binary search over their first
 // blocks: from a plan in device memory (M <= 64) ...
 template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R, int OCC>
-__global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_plan_kernel(const DecodeEntry* __restrict__ entries, int count, int m) {
+__global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_plan_kernel(const DecodeEntry* __restrict__ entries, const int32_t* __restrict__ first, int count, int m) {
     using C = Cfg<TM, TN, NW, KW, XK, CK, W, R>;
     __shared__ __align__(16) uint8_t s_lds[C::LdsBytes];
     const int64_t b = blockIdx.x;
+    const int blocks_m = (m + C::kRowsM - 1) / C::kRowsM;
     int lo = 0, hi = count - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;
-        if (entries[mid].first_step <= b) lo = mid;
+        if ((int64_t)first[mid] * blocks_m <= b) lo = mid;
         else hi = mid - 1;
     }
     const DecodeEntry& e = entries[lo];
     const GemmArgs a{e.packed, e.scales, e.x, e.y, e.n, e.ng, m};
-    const int blocks_m = (m + C::kRowsM - 1) / C::kRowsM;
-    run_tile<C, TM, TN, NW, KW, XK, CK, W, R>(a, (int)(b - e.first_step), blocks_m, (lds_u8*)s_lds);
+    run_tile<C, TM, TN, NW, KW, XK, CK, W, R>(a, (int)(b - (int64_t)first[lo] * blocks_m), blocks_m, (lds_u8*)s_lds);
 }
 
 // ... or from the launch's own arguments (prompts: no plan to keep).
@@ -825,7 +825,7 @@ struct Config {
     int occ;  // blocks per CU
     int rows_m, rows_n;
     hipError_t (*one)(const GemmArgs&, int64_t, int, hipStream_t);
-    hipError_t (*plan)(const DecodeEntry*, int, int64_t, int, hipStream_t);
+    hipError_t (*plan)(const DecodeEntry*, const int32_t*, int, int64_t, int, hipStream_t);
     hipError_t (*list)(const GemmList&, int64_t, hipStream_t);
 };
 
@@ -835,9 +835,11 @@ hipError_t launch_one(const GemmArgs& a, int64_t blocks, int blocks_m, hipStream
     return hipGetLastError();
 }
 template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R, int OCC>
-hipError_t launch_plan(const DecodeEntry* entries, int count, int64_t blocks, int m, hipStream_t stream) {
+hipError_t launch_plan(const DecodeEntry* entries, const int32_t* first, int count, int64_t blocks, int m, hipStream_t stream) {
     if constexpr (TM <= 4) {
-        hipLaunchKernelGGL((gemm_plan_kernel<TM, TN, NW, KW, XK, CK, W, R, OCC>), dim3((unsigned)blocks), dim3(NW * KW * kWave), 0, stream, entries, count, m);
+        using C = Cfg<TM, TN, NW, KW, XK, CK, W, R>;
+        static_assert(C::kRowsN >= 16 && C::kRowsN < 16 << kGemmPlanSizes && (C::kRowsN & (C::kRowsN - 1)) == 0, "plans hold these sizes");
+        hipLaunchKernelGGL((gemm_plan_kernel<TM, TN, NW, KW, XK, CK, W, R, OCC>), dim3((unsigned)blocks), dim3(NW * KW * kWave), 0, stream, entries, first, count, m);
         return hipGetLastError();
     } else {
         return hipErrorInvalidValue;  // plans are made for M <= 64 only
@@ -968,12 +970,16 @@ int gemm_plan_config(const wq_linear* lin, int count, int64_t m) {
     return pick_config(s.data(), n, m);
 }
 
-int gemm_plan_rows(int config) { return kConfigs[config].rows_n; }
+int gemm_plan_size(int config) {
+    int size = 0;
+    while ((16 << size) < kConfigs[config].rows_n) ++size;
+    return size;
+}
 
-int64_t gemm_plan_blocks_m(int config, int64_t m) { return (m + kConfigs[config].rows_m - 1) / kConfigs[config].rows_m; }
-
-hipError_t launch_gemm_plan(int config, const DecodeEntry* entries, int count, int64_t blocks, int m, hipStream_t stream) {
-    return kConfigs[config].plan(entries, count, blocks, m, stream);
+hipError_t launch_gemm_plan(int config, const DecodeEntry* entries, const int32_t* first, int count, int64_t blocks_n,
+                            int m, hipStream_t stream) {
+    const Config& c = kConfigs[config];
+    return c.plan(entries, first, count, blocks_n * ((m + c.rows_m - 1) / c.rows_m), m, stream);
 }
 
 hipError_t launch_gemm(const uint32_t* packed, const uint16_t* scales, const uint16_t* x, uint16_t* y, int64_t n,

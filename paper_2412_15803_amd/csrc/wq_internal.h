@@ -104,13 +104,16 @@ struct DecodePlan {
 };
 
 // Small-batch decode step: independent linears in one launch of the
-// matrix-core kernel.  The block shape is picked for the whole list; entry i
-// owns blocks [first_step, first_step + steps) of the grid, ceil(n / rows) x
-// blocks_m of them.
+// matrix-core kernel.  The block shape is picked for the whole list and the
+// number of rows m; its blocks span 16 << gemm_plan_size(config) rows of W.
+// Entry i owns the blocks from first[i] * blocks_m on, ceil(n / rows) x
+// blocks_m of them.  The plan holds `first` for every size, so that it does
+// not depend on m and one resident copy serves all batches of a list.
+constexpr int kGemmPlanSizes = 5;
 int gemm_plan_config(const wq_linear* lin, int count, int64_t m);
-int gemm_plan_rows(int config);
-int64_t gemm_plan_blocks_m(int config, int64_t m);
-hipError_t launch_gemm_plan(int config, const DecodeEntry* entries, int count, int64_t blocks, int m, hipStream_t stream);
+int gemm_plan_size(int config);
+hipError_t launch_gemm_plan(int config, const DecodeEntry* entries, const int32_t* first, int count, int64_t blocks_n,
+                            int m, hipStream_t stream);
 
 // Small-batch decode step below kMatrixCoreMinM rows (or any small batch when
 // forced): independent linears in

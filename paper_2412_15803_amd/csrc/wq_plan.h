@@ -162,9 +162,10 @@ struct GroupPlan {
 // blocks (matrix cores) or waves (vector kernel) of the grid.
 struct BatchPlan {
     size_t off_entries;
+    size_t off_first;  // first blocks of the entries (matrix cores)
     int count;
-    int64_t blocks;
-    int config;  // block shape (matrix cores)
+    int64_t blocks;    // of one set of rows of x (matrix cores), or waves
+    int config;        // block shape (matrix cores)
 };
 
 // Append the batch-1 plan of linears [g.begin, g.end); `capacity4` and
@@ -172,7 +173,8 @@ struct BatchPlan {
 // wide grouped kernels.
 GroupPlan plan_group(const wq_linear* lin, const Group& g, int capacity4, int capacity8, PlanBuf& out);
 
-// Append the matrix-core (M >= kMatrixCoreMinM) plan of a group at m rows.
+// Append the matrix-core (M >= kMatrixCoreMinM) plan of a group, whose bytes
+// are the same for every m, and pick the block shape at m rows.
 BatchPlan plan_batch_group(const wq_linear* lin, const Group& g, int64_t m, PlanBuf& out);
 
 // Append the vector small-batch (M < 8) plan of a group, `target` waves.

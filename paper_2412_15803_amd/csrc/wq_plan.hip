@@ -149,29 +149,31 @@ BatchPlan plan_batch_group(const wq_linear* lin, const Group& g, int64_t m, Plan
     bp.count = count;
     bp.config = gemm_plan_config(lin + g.begin, count, m);
     bp.off_entries = align16(out.size);
-    const size_t end = align16(bp.off_entries + sizeof(DecodeEntry) * count);
+    bp.off_first = align16(bp.off_entries + sizeof(DecodeEntry) * count);
+    const size_t end = align16(bp.off_first + sizeof(int32_t) * kGemmPlanSizes * count);
     if (out.overflow || end > out.cap) {
         out.overflow = true;
         return bp;
     }
     std::memset(out.data + out.size, 0, end - out.size);
     DecodeEntry* ents = reinterpret_cast<DecodeEntry*>(out.data + bp.off_entries);
-    const int rows = gemm_plan_rows(bp.config);
-    const int64_t blocks_m = gemm_plan_blocks_m(bp.config, m);
     for (int i = 0; i < count; ++i) fill_entry(ents[i], lin[g.begin + i]);
     // The longest K first, so that the launch ends on short blocks (sorted
     // in place, without allocating).
     std::sort(ents, ents + count, [](const DecodeEntry& a, const DecodeEntry& b) {
         return a.ng != b.ng ? a.ng > b.ng : a.packed != b.packed ? a.packed < b.packed : a.y < b.y;
     });
-    int64_t blocks = 0;
-    for (int i = 0; i < count; ++i) {
-        DecodeEntry& e = ents[i];
-        e.first_step = blocks;
-        e.steps = (e.n + rows - 1) / rows * blocks_m;
-        blocks += e.steps;
+    int32_t* first = reinterpret_cast<int32_t*>(out.data + bp.off_first);
+    for (int size = 0; size < kGemmPlanSizes; ++size, first += count) {
+        const int64_t rows = 16 << size;
+        int64_t blocks = 0;
+        for (int i = 0; i < count; ++i) {
+            first[i] = (int32_t)blocks;  // a group has at most kGroupMaxRows rows
+            blocks += (ents[i].n + rows - 1) / rows;
+        }
+        if (size == gemm_plan_size(bp.config)) bp.blocks = blocks;
     }
-    bp.blocks = blocks;
+    bp.off_first += sizeof(int32_t) * gemm_plan_size(bp.config) * count;
     out.size = end;
     return bp;
 }
@@ -258,7 +260,8 @@ hipError_t launch_groups(const wq_linear* lin, const Group* groups, int ngroups,
             const BatchPlan& bp = bplans[i];
             const DecodeEntry* ents = reinterpret_cast<const DecodeEntry*>(d_plan + bp.off_entries);
             if (matrix) {
-                e = launch_gemm_plan(bp.config, ents, bp.count, bp.blocks, (int)m, stream);
+                const int32_t* first = reinterpret_cast<const int32_t*>(d_plan + bp.off_first);
+                e = launch_gemm_plan(bp.config, ents, first, bp.count, bp.blocks, (int)m, stream);
             } else {
                 for (int64_t m0 = 0; m0 < m && e == hipSuccess; m0 += 8)
                     e = launch_grouped_mb(ents, bp.count, bp.blocks, m0, (int)std::min<int64_t>(8, m - m0), stream);

@@ -499,6 +499,41 @@ def test_alternating_lists_stay_correct():
         _check_set(host, lins, f"list {i}")
 
 
+def test_capture_of_another_batch_of_a_resident_list():
+    """The resident plan of a list serves every batch on the matrix cores:
+    after one eager call at M = 3 the same buffers' calls at 5, 16 and 40 rows
+    are captured, although their block shapes differ, and replay right."""
+    import torch
+
+    from paper_2412_15803_amd import wq
+
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    host, dev = [], []
+    for i, (n, k) in enumerate([(5120, 512), (300, 1024), (17, 96), (2048, 512)]):
+        p, sc, x = wl.random_words_host(i, n, k), wl.pow2_scales_host(i + 10, n, k), wl.small_int_x_host(i + 20, 40, k)
+        host.append((p, sc, x))
+        dev.append((to_dev(p), to_dev(sc), to_dev(x), torch.empty((40, n), dtype=torch.float16, device="cuda")))
+    rows = lambda m: [(p, sc, x[:m], y.view(-1)[:m * y.shape[1]].view(m, -1)) for p, sc, x, y in dev]  # noqa: E731
+    with torch.cuda.stream(s):
+        wq.wq_decode_linears(rows(3), m=3)
+    s.synchronize()
+    for m in (5, 16, 40):
+        announce(f"decode capture at M={m} of a list resident from M=3")
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            wq.wq_decode_linears(rows(m), m=m, stream=s)
+        for _ in range(2):
+            for lin in dev:
+                lin[3].fill_(float("nan"))
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            for (p, sc, x), (_, _, _, y) in zip(host, rows(m)):
+                ref = oracle.gemv(p, sc, x[:m], p.shape[0], x.shape[1])
+                assert np.array_equal(to_host(y, np.uint16), ref.view(np.uint16))
+
+
 def test_capture_needs_a_resident_plan():
     """Capturing a call whose plan is not on the device yet is refused
     (WQ_ERR_UNSUPPORTED, nothing recorded); after one eager call on the same
