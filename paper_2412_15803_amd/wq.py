@@ -173,6 +173,8 @@ def _stream(stream, t):
     """The handle of `stream`, or of the current stream of the device of `t`."""
     if stream is not None:
         return stream.cuda_stream
+    if not t.is_cuda:  # a marshalled list's own tensors are not looked at again
+        raise ValueError(f"expected a device tensor (got {t.device})")
     if _raw_stream is not None:
         return _raw_stream(t.get_device())
     return _torch.cuda.current_stream(t.device).cuda_stream

@@ -360,3 +360,19 @@ def test_fused_rejects_call_level(L):
     # residual equal to y (an in-place add) is accepted by validation
     ok = _fused(1, {(0, "residual"): 0x13000000})
     assert ok[0].residual == ok[0].y
+
+
+def test_host_tensor_beside_a_marshalled_list_is_refused(L):
+    """A list passed with a marshalled array is not checked tensor by tensor;
+    its x still has to be a device tensor, whose current stream is taken."""
+    import torch
+
+    from paper_2412_15803_amd import wq
+
+    x = torch.zeros((1, 64), dtype=torch.float16)
+    lin = [(None, None, x, None)]
+    for call in (wq.wq_decode_linears, wq.wq_decode_linears_noalloc):
+        with pytest.raises(ValueError, match="device"):
+            call(lin, _array=_linears(1))
+    with pytest.raises(ValueError, match="device"):
+        wq.wq_fused_linears([dict(x=x)], _array=_fused(1))
