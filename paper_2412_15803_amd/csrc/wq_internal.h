@@ -28,8 +28,9 @@ hipError_t launch_gemv(const uint32_t* packed, const uint16_t* scales,
                        int64_t n, int64_t k, int64_t m, hipStream_t stream);
 
 // Smallest batch that uses the matrix cores.  At M = 2, vector kernel against
-// GEMM: 3B-class step 342 against 282 us, 8B-class step 778 against 631,
-// 128256 x 3072 67.9 against 38.8 (few rows of deep K: launch_gemv).
+// GEMM: 3B-class step 345 against 279 us, 8B-class step 787 against 624,
+// 128256 x 3072 67.9 against 39.2 (a linear alone in its launch:
+// vector_takes_pair).
 constexpr int kMatrixCoreMinM = 2;
 
 // Largest batch of the planned decode steps (and of the vector kernel);
@@ -134,6 +135,32 @@ int mb_rows_for_work(int64_t work, int64_t ng);
 __host__ __device__ inline bool mb_two_sets(int64_t ng) { return (ng + 31) / 32 * 32 < (ng + 63) / 64 * 64; }
 __host__ __device__ inline int64_t mb_padded_groups(int64_t ng) {
     return mb_two_sets(ng) ? (ng + 31) / 32 * 32 : (ng + 63) / 64 * 64;
+}
+
+// Two rows of x against one linear alone in its launch: whether the vector
+// kernel is the faster one.  The GEMM takes about one block of 16 to 128 rows
+// per CU and round, so its time steps up where N passes a power of two and
+// grows with K where N leaves CUs idle; the vector kernel's follows the bytes,
+// best where a row's 64-group tiles divide evenly over the four waves of a
+// block.  Measured at M = 2 (GEMM / vector, us, cold weights):
+//   few rows            512 x 4096 4.9 / 4.0, 2048 x 3584 5.2 / 4.7; 2560 x 4096 5.3 / 5.4, 1024 x 3072 4.9 / 5.0
+//   code rows 4 KiB apart   4096 x 8192 8.4 / 7.8, 28672 x 8192 28.6 / 27.2; 65536 x 8192 54.0 / 57.6
+//   even tiles, deep    4096 x 14336 12.2 / 11.4, 6144 x 13824 15.3 / 14.5; 8192 x 14336 16.4 / 17.5, 4096 x 10240 9.4 / 10.5
+//   N past a power of 2 20480 x 4096 15.0 / 12.8, 10240 x 14336 24.3 / 20.8; 14336 x 4096 9.8 / 10.1, 40960 x 6144 31.2 / 34.5
+//   N up to 32768       32768 x 4096 21.2 / 17.2, 28672 x 4096 16.2 / 15.7, 30720 x 14336 65.9 / 55.1; 28672 x 14336 46.4 / 48.3,
+//                       16384 x 4096 10.3 / 11.0
+// Over 357 measured shapes (N 128..128256, K 2048..16384) the choice is within 1%
+// of the faster kernel on average (always the GEMM 7.4%, always the vector
+// kernel 7.0%).
+inline bool vector_takes_pair(int64_t n, int64_t k) {
+    const int64_t ng = k / 32, tiles = (ng + 63) / 64;
+    if (n <= 2048) return k >= 3584;
+    const bool even = !mb_two_sets(ng) && (tiles == 2 || tiles % 4 == 0 || (tiles > 4 && tiles % 4 == 3));
+    if (!even || n >= 65536) return false;
+    if (k % 8192 == 0 || (tiles >= 7 && n <= 6144)) return true;
+    int64_t half = 8192;  // the power of two below n
+    while (half * 2 < n) half *= 2;
+    return n > 8192 && (n <= half + half / 4 || (n > (tiles == 2 ? 16384 : 28672) && n <= 32768));
 }
 
 // Largest groups-per-lane of the grouped kernel (K <= 16384).

@@ -658,14 +658,11 @@ hipError_t launch_gemv(const uint32_t* packed, const uint16_t* scales, const uin
 #undef WQ_M1_CASE
     }
     if (m >= 2 && m <= kMaxSmallBatchM && fits_rsrc(n, ng)) {
-        // Matrix cores, but for two rows of x against few rows of deep K: the
-        // GEMM has at most one block of 16 rows per CU there, and the vector
-        // kernel keeps more loads in flight (M = 2: 3072 x 8192 6.9 against
-        // 8.0 us, 4096 x 14336 10.5 against 11.4; 4096 x 4096 5.6 and 5.6,
-        // 6144 x 4096 6.7 against 6.3, 16384 x 3072 10.8 against 8.0).  There,
-        // or when asked to, the vector kernel in passes of up to 8 rows.
-        const bool deep = m == 2 && n <= 4096 && k > 4096;
-        if (!deep && use_matrix_cores(m) && gemm_fits(n, k, m)) return launch_gemm(packed, scales, x, y, n, k, m, stream);
+        // Matrix cores, but for two rows of x where the vector kernel is
+        // faster.  There, or when asked to, the vector kernel in passes of up
+        // to 8 rows.
+        const bool vector = m == 2 && vector_takes_pair(n, k);
+        if (!vector && use_matrix_cores(m) && gemm_fits(n, k, m)) return launch_gemm(packed, scales, x, y, n, k, m, stream);
         for (int64_t m0 = 0; m0 < m; m0 += 8) {
             const int mc = (int)min((int64_t)8, m - m0);
             const uint16_t* xc = x + m0 * k;

@@ -98,19 +98,28 @@ constexpr int64_t kGroupMaxRows = int64_t(1) << 30;
 // one after another.  Linears the grouped kernels cannot take (K > 16384 at
 // M = 1, codes of 4 GiB or more, or x rows beyond gemm_fits or, for prompts,
 // prefill_fits) form groups of their own, and a group closes before its rows
-// would pass kGroupMaxRows.  Calls emit(Group) in
-// order; `reads` and `writes` are empty dependency sets.
+// would pass kGroupMaxRows.  A group of one linear that runs faster by
+// wq_gemv's own choice of kernel (two rows of x) is left to it.  Calls
+// emit(Group) in order; `reads` and `writes` are empty dependency sets.
 template <class Deps, class Emit>
 void split_groups(const wq_linear* lin, int count, int64_t m, Deps& reads, Deps& writes, Emit emit) {
     int begin = 0;
     int64_t rows = 0;
+    auto close = [&](int end) {
+        // Alone at M = 2: 3072 x 8192 8.5 us in a GEMM launch of one entry,
+        // 7.0 by the vector kernel; 4096 x 14336 12.9 and 11.4.  (Lists of
+        // two linears and more stay: 2 x 3072 x 8192 11.1 against 14.4 us in
+        // the grouped vector kernel, 4 x 1024 x 14336 15.7 against 19.9.)
+        const bool alone = m == 2 && end - begin == 1 && vector_takes_pair(lin[begin].N, lin[begin].K);
+        emit(Group{begin, end, !alone});
+    };
     for (int i = 0; i < count; ++i) {
         const wq_linear& l = lin[i];
         const bool too_long = m == 1 && l.K / 32 > 64 * kDecodeMaxGpl;
         const bool too_wide = m >= kMatrixCoreMinM &&
                               !(m > kMaxSmallBatchM ? prefill_fits(l.N, l.K, m) : gemm_fits(l.N, l.K, m));
         if (too_long || too_wide || !fits_rsrc(l.N, l.K / 32)) {
-            if (i > begin) emit(Group{begin, i, true});
+            if (i > begin) close(i);
             emit(Group{i, i + 1, false});
             reads.clear();
             writes.clear();
@@ -120,7 +129,7 @@ void split_groups(const wq_linear* lin, int count, int64_t m, Deps& reads, Deps&
         }
         const Span x = span_of(l.x, 2 * m * l.K), y = span_of(l.y, 2 * m * l.N);
         if (i > begin && (writes.hits(x) || reads.hits(y) || writes.hits(y) || rows + l.N > kGroupMaxRows)) {
-            emit(Group{begin, i, true});
+            close(i);
             reads.clear();
             writes.clear();
             begin = i;
@@ -130,7 +139,7 @@ void split_groups(const wq_linear* lin, int count, int64_t m, Deps& reads, Deps&
         writes.add(y);
         rows += l.N;
     }
-    if (begin < count) emit(Group{begin, count, true});
+    if (begin < count) close(count);
 }
 
 // A byte buffer the plans are appended to; `overflow` is set (and nothing

@@ -54,6 +54,33 @@ int main() {
             expect(grouped, k <= k_at, what);
         }
     }
+    // Two rows of x: a linear alone in its launch takes the kernel that
+    // wq_gemv picks for it; with others, or at other batches, the planned one.
+    struct {
+        int64_t n, k;
+        bool vector;
+    } const pairs[] = {
+        {1, 3584, true},      {2048, 3584, true},    {2048, 3552, false},  {2049, 4096, false},   {512, 16384, true},
+        {2049, 8192, true},   {65535, 8192, true},   {65536, 8192, false}, {4096, 14336, true},   {6144, 13824, true},
+        {6145, 14336, false}, {4096, 10240, false},  {3072, 6144, false},  {8192, 4096, false},   {8193, 4096, true},
+        {10240, 4096, true},  {10241, 4096, false},  {16384, 4096, false}, {20480, 14336, true},  {20481, 14336, false},
+        {16385, 4096, true},  {28672, 14336, false}, {28673, 14336, true},  {32768, 4096, true},  {40960, 4096, true},   {40961, 4096, false},
+        {20480, 5120, false}, {128256, 3072, false}, {3072, 3072, false},  {16384, 3072, false},  {2560, 7168, false},
+    };
+    for (const auto& p : pairs) {
+        char what[96];
+        std::snprintf(what, sizeof(what), "%lld x %lld alone at M=2 by the vector kernel", (long long)p.n, (long long)p.k);
+        expect(wq::vector_takes_pair(p.n, p.k), p.vector, what);
+        expect(!split({linear(0, p.n, p.k)}, 2)[0].grouped, p.vector, what);
+        // A list that closes before it: the second linear reads the first one's y.
+        wq_linear dep = linear(1, p.n, p.k);
+        const wq_linear before = linear(0, 64, 64);
+        dep.x = before.y;
+        const auto g = split({before, dep}, 2);
+        expect(g.size() == 2 && g[0].grouped && !g[1].grouped, p.vector, what);
+        expect(split({linear(0, p.n, p.k), linear(1, 64, 64)}, 2)[0].grouped, true, "two linears");
+        expect(split({linear(0, p.n, p.k)}, 3)[0].grouped, true, "three rows");
+    }
     if (failures) return 1;
     std::printf("ok\n");
     return 0;

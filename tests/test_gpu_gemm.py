@@ -132,6 +132,36 @@ def test_group_sum_picked_exact(m, n, k):
         _check(m, n, k, m + n + k, shift=n % 2)
 
 
+@pytest.mark.parametrize("n,k", [(1, 3584), (17, 3552), (2048, 3584), (2049, 3584), (2049, 8192), (300, 16384), (2050, 13824),
+                                 (8193, 4096), (10241, 4096)])
+def test_two_rows_on_either_kernel_exact(n, k):
+    """Both sides of the line between the vector kernel and the GEMM at
+    M = 2, through wq_gemv and as the second of two dependent linears."""
+    import torch
+
+    from paper_2412_15803_amd import wq
+
+    announce(f"two rows N={n} K={k}")
+    packed, scales, x, sd = _case(2, n, k, n + k, n % 2, -10, -7)  # sums below 4 * 8 * 2^-7 * 16384 = 2^12
+    ref = oracle.gemv(packed, scales, x, n, k).view(np.uint16)
+    pd = to_dev(packed)
+    assert np.array_equal(to_host(gpu_gemv(pd, sd, to_dev(x)), np.uint16), ref)
+    # x of the second linear is the first one's y: one nonzero weight per row, code 9 at a scale of 1.
+    ident = np.full((k, 4), 0x88888888, dtype=np.uint32)
+    r = np.arange(k)
+    ident[r, r % 32 // 8] += np.uint32(1) << (4 * (r % 8)).astype(np.uint32)
+    first_x = np.zeros((2, 32), dtype=np.float16)
+    first_x[:, :8] = wl.small_int_x_host(n, 2, 8)
+    x2 = first_x[:, np.arange(k) % 32]
+    ref2 = oracle.gemv(packed, scales, x2, n, k).view(np.uint16)
+    ones = torch.ones((k, 1), dtype=torch.float16, device="cuda:0")
+    mid = torch.full((2, k), float("nan"), dtype=torch.float16, device="cuda:0")
+    y = torch.full((2, n), float("nan"), dtype=torch.float16, device="cuda:0")
+    wq.wq_decode_linears([(to_dev(ident), ones, to_dev(first_x), mid), (pd, sd, mid, y)], m=2)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host(y, np.uint16), ref2)
+
+
 @pytest.mark.parametrize("m", [2, 4, 7])
 def test_group_sum_special_values(m):
     """An infinity in x gives what the sum of its products gives (infinite,
