@@ -213,7 +213,7 @@ struct Cfg {
     static_assert(XBytes % 1024 == 0, "x loads are whole");
     static_assert(W == 2 || W == 4, "the next window is complete before the last stage of a window");
     static_assert(CSlotBytes % 1024 == 0 && SBytes % 1024 == 0, "slot loads are whole");
-    static_assert(CK == XK || (CK == kStageK && QS <= 2), "code slots");
+    static_assert((CK == kStageK && XK == 128) || (CK == 64 && XK == 64), "code slots");
 };
 
 struct GemmArgs {
@@ -239,8 +239,7 @@ template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R>
 __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int64_t m0, int turn, lds_u8* lds) {
     using C = Cfg<TM, TN, NW, KW, XK, CK, W, R>;
     constexpr int QS = C::QS, NX = C::NX, NC = C::NC, NS = C::NS;
-    constexpr int HS = XK >= 128 ? XK / 128 : 1;  // 128-deep parts of an x stage
-    constexpr int WPL = XK >= 128 ? 4 : XK / 32;  // words per lane of a part
+    constexpr int WPL = XK / 32;  // words per lane of an x stage
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int wn = wave % NW, wk = wave / NW;
@@ -278,8 +277,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
     };
     // x: one load covers XR rows of an x stage, 16-byte chunks XOR-placed by row.
     constexpr int XCH = XK / 8;       // chunks per row
-    constexpr int XR = 64 / XCH > 0 ? 64 / XCH : 1;
-    static_assert(XCH <= 32 && (XR >= 2), "x rows per load");
+    constexpr int XR = 64 / XCH;      // rows per load
     auto issue_x = [&](int st, bool ok, int q, int buf) {
         const int k0 = st * kStageK + q * XK;
 #pragma unroll
@@ -335,18 +333,17 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
 
-    // Operand A of part h (128 or 64 deep) of x buffer `buf`.
-    constexpr int HP = CK == kStageK && QS == 1 ? HS : 1;  // parts held at once
-    half8 fa[HP][TM][WPL];
-    auto load_a = [&](int buf, int h, int slot) {
+    // Operand A, of x buffer `buf`: word t, or all of them.
+    half8 fa[TM][WPL];
+    auto load_word = [&](int buf, int t) {
+        const int ch = WPL * c + t;
+        const uint32_t off = xlds + buf * C::XBytes + (uint32_t)li * (XK * 2) + (uint32_t)((ch ^ place<XK * 2>(li)) * 16);
 #pragma unroll
-        for (int t = 0; t < WPL; ++t) {
-            const int ch = h * 16 + WPL * c + t;
-            const uint32_t off = xlds + buf * C::XBytes + (uint32_t)li * (XK * 2) + (uint32_t)((ch ^ place<XK * 2>(li)) * 16);
+        for (int i = 0; i < TM; ++i) fa[i][t] = *at<const half8>(off + i * 16 * XK * 2);
+    };
+    auto load_a = [&](int buf) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-                fa[slot][i][t] = *at<const half8>(off + i * 16 * XK * 2);
-        }
+        for (int t = 0; t < WPL; ++t) load_word(buf, t);
     };
     // The lane's scale of group g (0..7) of a stage, `it` stages into the range,
     // of row li; the other tiles' lie 16 rows on.
@@ -378,9 +375,9 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
         const half2v s = as_h2(pair);
         return Scales{s, s * k1024 * k1024, s * km8};
     };
-    // Multiplies of tile tt with the part of x in `slot`; the scale is half h
-    // of its pair.
-    auto multiply = [&](auto small, const uint32_t* wd, const Scales& sc, int h, int slot, int tt) {
+    // Multiplies of tile tt with the x in `fa`; the scale is half h of its
+    // pair.
+    auto multiply = [&](auto small, const uint32_t* wd, const Scales& sc, int h, int tt) {
         auto both = [&](half2v v) { return half2v{v[h], v[h]}; };
         constexpr bool fast = decltype(small)::value;
         if constexpr (R == 4) {
@@ -392,7 +389,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 const half8 fb = codes8(wd[t]);
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
-                    d[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[slot][i][t], fb, d[i], 0, 0, 0);
+                    d[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[i][t], fb, d[i], 0, 0, 0);
             }
             const float s = (float)sc.s[h] * 0x1p20f;
 #pragma unroll
@@ -408,7 +405,7 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
             else fb = dequant8(wd[t], both(sc.s));
 #pragma unroll
             for (int i = 0; i < TM; ++i)
-                acc[i][tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[slot][i][t], fb, acc[i][tt], 0, 0, 0);
+                acc[i][tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[i][t], fb, acc[i][tt], 0, 0, 0);
         }
     };
     // Whether every lane's scales allow the short dequantization.
@@ -465,95 +462,60 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
             issue_codes(st, ok, 0, 2 * tt);
             issue_codes(st, ok, 0, 2 * tt + 1);
         };
-        if constexpr (QS == 1) {
-            for (int it = 0, st = start; it < iters; ++it, st = after(st, 1)) {
-                const int next = after(st, 1), buf = it & 1;
-                const bool more = it + 1 < range;
-                wait_dma<2 * TN>();  // x and scales of the stage; codes may be in flight
-                block_sync<NW>();
-                issue_x(next, more, 0, buf ^ 1);
-                const bool win = it % W == 0;  // a scale window starts: load the next one
-                if (win) issue_scales(it / W + 1, after(st, W));
+        // Two x stages: the second half of every tile waits in registers.
+        // The first half of the tiles is refilled in the first x stage,
+        // the others in the second.
+        constexpr int TH = (TN + 1) / 2;
+        for (int it = 0, st = start; it < iters; ++it, st = after(st, 1)) {
+            const int next = after(st, 1);
+            const bool more = it + 1 < range;
+            Tile T[TN];
+            if (it == 0) wait_dma<2 * TN>();
+            else wait_dma<2 * (TN - TH)>();
+            block_sync<NW>();
+            if (it % W == 0) issue_scales(it / W + 1, after(st, W));
+            issue_x(st, it < range, 1, 1);
+            load_a(0);
+            const uint32_t mx = read_scales(it, st);
+            const bool small = R == 16 && all_small(mx);  // R = 4 has one form
+            auto first = [&](auto sm) {
+                // Newer than tile 0's codes: at most every other tile's and x.
+                if (it == 0) wait_dma<2 * (TN - 1) + NX>();
+                read_tile(T[0], 0);
 #pragma unroll
-                for (int h = 0; h < HS; ++h) load_a(buf, h, h);
-                const bool small = all_small(read_scales(it, st));
-                auto body = [&](auto sm) {
-                    Tile T[2];
-                    if (win) wait_dma<2 * (TN - 1) + NX + NS>();
-                    else wait_dma<2 * (TN - 1) + NX>();
-                    read_tile(T[0], 0);
-#pragma unroll
-                    for (int tt = 0; tt < TN; ++tt) {
-                        if (tt + 1 < TN) {
-                            if (win) wait_dma<2 * (TN > 1 ? TN - 2 : 0) + NX + NS>();
-                            else wait_dma<2 * (TN > 1 ? TN - 2 : 0) + NX>();
-                            read_tile(T[(tt + 1) & 1], tt + 1);
+                for (int tt = 0; tt < TN; ++tt) {
+                    if (tt + 1 < TN) {
+                        if (it == 0 || tt + 1 >= TH) {
+                            // Old codes after tile tt + 1, x, refills so far.
+                            constexpr int base = NX;
+                            const int n = 2 * (TN - 2 - tt) + base + 2 * (tt < TH ? tt : TH);
+                            if (n >= base + 6) wait_dma<base + 6>();
+                            else if (n >= base + 4) wait_dma<base + 4>();
+                            else if (n >= base + 2) wait_dma<base + 2>();
+                            else wait_dma<base>();
                         }
-                        tile_read_done(T[tt & 1]);
-                        refill(next, more, tt);
-#pragma unroll
-                        for (int h = 0; h < HS; ++h) multiply(sm, T[tt & 1].w[h], scales_of(pair[tt]), h, h, tt);
+                        read_tile(T[tt + 1], tt + 1);
                     }
-                };
-                if (small) body(Small{});
-                else body(Any{});
-            }
-        } else {
-            // Two x stages: the second half of every tile waits in registers.
-            // The first half of the tiles is refilled in the first x stage,
-            // the others in the second.
-            constexpr int TH = (TN + 1) / 2;
-            for (int it = 0, st = start; it < iters; ++it, st = after(st, 1)) {
-                const int next = after(st, 1);
-                const bool more = it + 1 < range;
-                Tile T[TN];
-                if (it == 0) wait_dma<2 * TN>();
-                else wait_dma<2 * (TN - TH)>();
-                block_sync<NW>();
-                if (it % W == 0) issue_scales(it / W + 1, after(st, W));
-                issue_x(st, it < range, 1, 1);
-                load_a(0, 0, 0);
-                const uint32_t mx = read_scales(it, st);
-                const bool small = R == 16 && all_small(mx);  // R = 4 has one form
-                auto first = [&](auto sm) {
-                    // Newer than tile 0's codes: at most every other tile's and x.
-                    if (it == 0) wait_dma<2 * (TN - 1) + NX>();
-                    read_tile(T[0], 0);
+                    tile_read_done(T[tt]);
+                    if (tt < TH) refill(next, more, tt);
+                    multiply(sm, T[tt].w[0], scales_of(pair[tt]), 0, tt);
+                }
+            };
+            auto second = [&](auto sm) {
 #pragma unroll
-                    for (int tt = 0; tt < TN; ++tt) {
-                        if (tt + 1 < TN) {
-                            if (it == 0 || tt + 1 >= TH) {
-                                // Old codes after tile tt + 1, x, refills so far.
-                                constexpr int base = NX;
-                                const int n = 2 * (TN - 2 - tt) + base + 2 * (tt < TH ? tt : TH);
-                                if (n >= base + 6) wait_dma<base + 6>();
-                                else if (n >= base + 4) wait_dma<base + 4>();
-                                else if (n >= base + 2) wait_dma<base + 2>();
-                                else wait_dma<base>();
-                            }
-                            read_tile(T[tt + 1], tt + 1);
-                        }
-                        tile_read_done(T[tt]);
-                        if (tt < TH) refill(next, more, tt);
-                        multiply(sm, T[tt].w[0], scales_of(pair[tt]), 0, 0, tt);
-                    }
-                };
-                auto second = [&](auto sm) {
-#pragma unroll
-                    for (int tt = 0; tt < TN; ++tt) {
-                        if (tt >= TH) refill(next, more, tt);
-                        multiply(sm, T[tt].w[1], scales_of(pair[tt]), 1, 0, tt);
-                    }
-                };
-                if (small) first(Small{});
-                else first(Any{});
-                wait_dma<2 * TH>();  // x stage 1
-                block_sync<NW>();
-                issue_x(next, more, 0, 0);
-                load_a(1, 0, 0);
-                if (small) second(Small{});
-                else second(Any{});
-            }
+                for (int tt = 0; tt < TN; ++tt) {
+                    if (tt >= TH) refill(next, more, tt);
+                    multiply(sm, T[tt].w[1], scales_of(pair[tt]), 1, tt);
+                }
+            };
+            if (small) first(Small{});
+            else first(Any{});
+            wait_dma<2 * TH>();  // x stage 1
+            block_sync<NW>();
+            issue_x(next, more, 0, 0);
+            load_a(1);
+            if (small) second(Small{});
+            else second(Any{});
         }
     } else {
         // One slot per x stage, each refilled for the next weight stage once
@@ -577,13 +539,6 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
                 }
                 // Words of the lane: WPL from word w0 of the stage's row.
                 const int w0 = q * (XK / 8) + WPL * c;
-                auto load_at = [&](int t) {
-                    const int ch = WPL * c + t;
-                    const uint32_t off = xlds + buf * C::XBytes + (uint32_t)li * (XK * 2) + (uint32_t)((ch ^ place<XK * 2>(li)) * 16);
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-                        fa[0][i][t] = *at<const half8>(off + i * 16 * XK * 2);
-                };
                 const uint32_t sa = scale_addr(w0 / 4, it);
                 const uint32_t keep = cut(it, st) ? keep_group(w0 / 4, it, st) : 0xFFFFu;
                 uint32_t wd[TN][WPL];
@@ -591,26 +546,21 @@ __device__ __forceinline__ void gemm_block(const GemmArgs& a, int64_t row0, int6
 #pragma unroll
                 for (int tt = 0; tt < TN; ++tt) {
                     const uint32_t ca = clds + q * C::CSlotBytes + (uint32_t)(16 * tt + li) * (CK / 2) + (uint32_t)(WPL * c) * 4;
-                    if constexpr (WPL == 4) {
-                        const u32x4 v = *at<const u32x4>(ca);
-                        wd[tt][0] = v.x; wd[tt][1] = v.y; wd[tt][2] = v.z; wd[tt][3] = v.w;
-                    } else {
-                        const u32x2 v = *at<const u32x2>(ca);
-                        wd[tt][0] = v.x; wd[tt][1] = v.y;
-                    }
+                    const u32x2 v = *at<const u32x2>(ca);
+                    wd[tt][0] = v.x; wd[tt][1] = v.y;
                     const uint32_t sv = read_scale(sa, tt) & keep;
                     sc[tt] = as_h2(sv | (sv << 16));
                 }
-                load_at(0);
+                load_word(buf, 0);
 #pragma unroll
                 for (int t = 0; t < WPL; ++t) {
-                    if (t + 1 < WPL) load_at(t + 1);
+                    if (t + 1 < WPL) load_word(buf, t + 1);
 #pragma unroll
                     for (int tt = 0; tt < TN; ++tt) {
                         const half8 fb = dequant8(wd[tt][t], sc[tt]);
 #pragma unroll
                         for (int i = 0; i < TM; ++i)
-                            acc[i][tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[0][i][t], fb, acc[i][tt], 0, 0, 0);
+                            acc[i][tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[i][t], fb, acc[i][tt], 0, 0, 0);
                     }
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
