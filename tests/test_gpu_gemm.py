@@ -1,7 +1,8 @@
 """GPU parity of the matrix-core GEMM's block shapes (wq_gemm.hip): every
-compiled shape (forced with WQ_GEMM_CONFIG) at sizes that leave remainders in
-M, N and K, with scales on both sides of the short dequantization's limit and
-scale arrays that start in the middle of a dword.
+compiled shape (forced with WQ_GEMM_CONFIG, in single, planned and listed
+launches) at sizes that leave remainders in M, N and K, with scales on both
+sides of the short dequantization's limit and scale arrays that start in the
+middle of a dword.
 
 Inputs are integer-exact: x in {-4..4} and scales 2^e, e in [-10, -2], so every
 product is a multiple of 2^-10 and every sum of K = 1056 of them at most
@@ -11,17 +12,37 @@ is unique up to its one fp16 rounding, so the comparison is bit for bit.
 
 from __future__ import annotations
 
+import os
+import re
+
 import numpy as np
 import pytest
 
 import oracle
 from gpu_util import announce, gpu_gemv, to_dev, to_host
 from paper_2412_15803_amd import workloads as wl
+from paper_2412_15803_amd import wq
 
 pytestmark = pytest.mark.gpu
 
-CONFIGS = 24  # rows of WQ_GEMM_CONFIGS; the first 5 take 16 rows of x per block
-ONE_TILE = 5
+
+
+def _block_shapes():
+    """The rows of the source's WQ_GEMM_CONFIGS: what index WQ_GEMM_CONFIG
+    names.  The library forces a shape on M > 64 if TM >= 2 and R = 16, on
+    2 <= M <= 64 if TM <= 4, and picks its own where it cannot."""
+    names = ("tm", "tn", "nw", "kw", "xk", "ck", "w", "r", "occ")
+    table = open(os.path.join(os.path.dirname(wq.__file__), "csrc", "wq_gemm.hip")).read()
+    table = table[table.index("#define WQ_GEMM_CONFIGS(X)"):table.index("struct Config {")]
+    return [dict(zip(names, map(int, row.split(",")))) for row in re.findall(r"X\(([\d, ]+)\)", table)]
+
+
+SHAPES = _block_shapes()
+TALL = [i for i, c in enumerate(SHAPES) if c["r"] == 16]  # 16 rows of x per tile, or each of 4 in four places
+SMALL_BATCH = [i for i, c in enumerate(SHAPES) if c["tm"] <= 4]
+PROMPT = [i for i in TALL if SHAPES[i]["tm"] >= 2]
+LINES = [i for i, c in enumerate(SHAPES) if c["ck"] == 256]
+assert len(SHAPES) >= 24 and len(LINES) >= 16 and all(SHAPES[i]["tm"] <= 4 for i in LINES)
 
 
 def _case(m, n, k, seed, shift=0, lo=-10, hi=-2):
@@ -45,14 +66,62 @@ def _check(m, n, k, seed, shift=0):
 
 
 @pytest.mark.parametrize("shift", [0, 1])
-@pytest.mark.parametrize("config", range(CONFIGS))
+@pytest.mark.parametrize("config", TALL)
 def test_block_shape_exact(config, shift, monkeypatch):
     """One block past a whole number of them in N, a ragged M over two or
     more blocks of rows, and K = 4 whole stages and one group."""
     monkeypatch.setenv("WQ_GEMM_CONFIG", str(config))
-    m = 19 if config < ONE_TILE else 131
+    m = 131 if config in PROMPT else 19
     announce(f"gemm config {config} M={m} N=530 K=1056 scale shift {shift}")
     _check(m, 530, 1056, 100 * config + shift, shift)
+
+
+def _check_list(m, shapes, seed, lo=-10, hi=-2):
+    """Independent linears through wq_decode_linears, every second one with
+    scales that start in the middle of a dword."""
+    import torch
+
+    cases = [_case(m, n, k, seed + 10 * i, i % 2, lo, hi) for i, (n, k) in enumerate(shapes)]
+    lins = [(to_dev(p), sd, to_dev(x), torch.full((m, p.shape[0]), float("nan"), dtype=torch.float16, device="cuda:0"))
+            for p, _, x, sd in cases]
+    wq.wq_decode_linears(lins, m=m)
+    torch.cuda.synchronize()
+    for (p, s, x, _), (*_, y), (n, k) in zip(cases, lins, shapes):
+        bad = np.argwhere(to_host(y, np.uint16) != oracle.gemv(p, s, x, n, k).view(np.uint16))
+        assert bad.size == 0, f"{n} x {k}: {len(bad)} mismatches, first {bad[:5].tolist()}"
+
+
+@pytest.mark.parametrize("config", SMALL_BATCH)
+def test_block_shape_planned_exact(config, monkeypatch):
+    """Several linears in one planned launch, a block of rows of x and part of
+    a second one where 64 rows allow it."""
+    monkeypatch.setenv("WQ_GEMM_CONFIG", str(config))
+    m = min(SHAPES[config]["r"] * SHAPES[config]["tm"] + 3, 61)
+    announce(f"gemm config {config} planned M={m}")
+    _check_list(m, [(275, 352), (530, 1056), (17, 96), (1, 32)], 300 * config)
+
+
+@pytest.mark.parametrize("config", PROMPT)
+def test_block_shape_listed_exact(config, monkeypatch):
+    monkeypatch.setenv("WQ_GEMM_CONFIG", str(config))
+    announce(f"gemm config {config} listed M=131")
+    _check_list(131, [(275, 352), (530, 1056), (17, 96), (1, 32)], 400 * config)
+
+
+@pytest.mark.parametrize("config", LINES)
+def test_block_shape_turned_exact(config, monkeypatch):
+    """K = 8192 and one block of rows of x: the blocks of a linear start their
+    walk along K at different windows, in single and in planned launches.
+    Sums below 4 * 8 * 2^-4 * 8192 = 2^14."""
+    monkeypatch.setenv("WQ_GEMM_CONFIG", str(config))
+    c = SHAPES[config]
+    m, rows = c["r"] * c["tm"] - 1, 16 * c["tn"] * c["nw"]
+    n = 3 * rows + 5
+    announce(f"gemm config {config} turned M={m} N={n}")
+    packed, scales, x, sd = _case(m, n, 8192, 500 * config, 0, -10, -4)
+    y = to_host(gpu_gemv(to_dev(packed), sd, to_dev(x)), np.uint16)
+    assert np.array_equal(y, oracle.gemv(packed, scales, x, n, 8192).view(np.uint16))
+    _check_list(m, [(rows + 5, 8192), (40, 64)], 600 * config, lo=-10, hi=-4)
 
 
 @pytest.mark.parametrize("m,n,k", [(3, 1, 32), (3, 17, 64), (16, 33, 2080), (17, 257, 96), (48, 65, 8224), (49, 31, 224),
@@ -86,8 +155,6 @@ def test_prompt_list_of_many_linears_exact():
     launch's worth of descriptors, in one call, bit for bit."""
     import torch
 
-    from paper_2412_15803_amd import wq
-
     m, lins, refs = 66, [], []
     announce("gemm list of 71 linears at M=66")
     for i in range(70):
@@ -107,7 +174,7 @@ def test_prompt_list_of_many_linears_exact():
 
 # Blocks that hold four rows of x per tile, each in the places of four lane
 # groups, so that a tile's sums are those of single groups.
-GROUP_CONFIGS = range(24, 31)  # the last one is the 16-row shape with K over eight waves
+GROUP_CONFIGS = [i for i, c in enumerate(SHAPES) if c["r"] == 4 or (c["tn"], c["kw"]) == (1, 8)]
 
 
 @pytest.mark.parametrize("m", [2, 3, 4, 5, 8, 19])
@@ -125,9 +192,8 @@ def test_group_sum_shape_exact(config, m, monkeypatch):
 def test_group_sum_picked_exact(m, n, k):
     announce(f"gemm M={m} N={n} K={k}")
     if k > 8224:  # keep every sum exact: at most 4 * 8 * 2^-4 * 16384 = 2^15
-        packed, scales, x, sd = _case(m, n, k, m + n, 1, -10, -4)
-        y = to_host(gpu_gemv(to_dev(packed), sd, to_dev(x)), np.uint16)
-        assert np.array_equal(y, oracle.gemv(packed, scales, x, n, k).view(np.uint16))
+        # In a list: alone, two rows of so deep a K take the vector kernel.
+        _check_list(m, [(n, k), (n, k)], m + n, lo=-10, hi=-4)
     else:
         _check(m, n, k, m + n + k, shift=n % 2)
 
@@ -138,8 +204,6 @@ def test_two_rows_on_either_kernel_exact(n, k):
     """Both sides of the line between the vector kernel and the GEMM at
     M = 2, through wq_gemv and as the second of two dependent linears."""
     import torch
-
-    from paper_2412_15803_amd import wq
 
     announce(f"two rows N={n} K={k}")
     packed, scales, x, sd = _case(2, n, k, n + k, n % 2, -10, -7)  # sums below 4 * 8 * 2^-7 * 16384 = 2^12
@@ -195,8 +259,6 @@ def test_outliers_at_zero_weights(m, scale, big):
     zero), among small ones: their products are exactly zero, so they add
     nothing to the documented bound and must add nothing to the error."""
     import torch
-
-    from paper_2412_15803_amd import wq
 
     n, k = 70, 352
     packed = wl.random_words_host(31 * m, n, k)
