@@ -173,11 +173,17 @@ def _stream(stream, t):
     """The handle of `stream`, or of the current stream of the device of `t`."""
     if stream is not None:
         return stream.cuda_stream
-    if not t.is_cuda:  # a marshalled list's own tensors are not looked at again
-        raise ValueError(f"expected a device tensor (got {t.device})")
     if _raw_stream is not None:
         return _raw_stream(t.get_device())
     return _torch.cuda.current_stream(t.device).cuda_stream
+
+
+def _unchecked_stream(stream, t):
+    """_stream for a tensor that the call has not looked at (a marshalled
+    list's, a buffer's): a host tensor has no stream."""
+    if stream is None and not t.is_cuda:
+        raise ValueError(f"expected a device tensor (got {t.device})")
+    return _stream(stream, t)
 
 
 def wq_pack(w, packed_w, scales, group: int = GROUP, stream=None) -> None:
@@ -232,7 +238,7 @@ def wq_decode_linears(linears, m: int = 1, group: int = GROUP, stream=None, _arr
     make_linear_array may be passed as _array to skip re-marshalling."""
     arr = _array if _array is not None else make_linear_array(linears, m, group)
     _torch or _load_torch()
-    _check((_lib or lib()).wq_decode_linears(arr, len(arr), m, group, _stream(stream, linears[0][2])))
+    _check((_lib or lib()).wq_decode_linears(arr, len(arr), m, group, _unchecked_stream(stream, linears[0][2])))
 
 
 def wq_decode_linears_noalloc(linears, m: int = 1, group: int = GROUP, stream=None, _array=None) -> None:
@@ -240,7 +246,7 @@ def wq_decode_linears_noalloc(linears, m: int = 1, group: int = GROUP, stream=No
     plan lives in the library's fixed per-device array; see include/wq.h)."""
     arr = _array if _array is not None else make_linear_array(linears, m, group)
     _torch or _load_torch()
-    _check((_lib or lib()).wq_decode_linears_noalloc(arr, len(arr), m, group, _stream(stream, linears[0][2])))
+    _check((_lib or lib()).wq_decode_linears_noalloc(arr, len(arr), m, group, _unchecked_stream(stream, linears[0][2])))
 
 
 # ------------------------------------------------------- paged attention
@@ -332,7 +338,7 @@ def wq_fused_linears(linears, argmax=None, group: int = GROUP, stream=None, _arr
     _torch or _load_torch()
     arr = _array if _array is not None else make_fused_array(linears, group)
     pa = _dev_tensor(argmax.reshape(-1), "argmax", _INTS, (1,)) if argmax is not None else None
-    _check((_lib or lib()).wq_fused_linears(arr, len(arr), pa, group, _stream(stream, linears[0]["x"])))
+    _check((_lib or lib()).wq_fused_linears(arr, len(arr), pa, group, _unchecked_stream(stream, linears[0]["x"])))
 
 
 def wq_fused_check(device=None, stream=None) -> None:
@@ -357,4 +363,4 @@ def stream_read(buf, sink, stream=None) -> None:
     if sink.device != buf.device or sink.dtype not in (torch.int32, torch.uint32) or sink.numel() < 1024:
         raise ValueError("sink must be a device int32 tensor of at least 1024 elements")
     _torch or _load_torch()
-    _check(lib().wq_stream_read(buf.data_ptr(), nbytes, sink.data_ptr(), _stream(stream, buf)))
+    _check(lib().wq_stream_read(buf.data_ptr(), nbytes, sink.data_ptr(), _unchecked_stream(stream, buf)))
