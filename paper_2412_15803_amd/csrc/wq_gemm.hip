@@ -674,23 +674,31 @@ __global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_kernel(const GemmArgs
     run_tile<C, TM, TN, NW, KW, XK, CK, W, R>(a, b, blocks_m, (lds_u8*)s_lds);
 }
 
+// Index of a block's rows of W among the sizes that plans hold.
+constexpr int plan_size(int rows_n) {
+    int size = 0;
+    while ((16 << size) < rows_n) ++size;
+    return size;
+}
+
 // Independent linears of one launch, found by binary search over their first
 // blocks: from a plan in device memory (M <= 64) ...
 template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R, int OCC>
-__global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_plan_kernel(const DecodeEntry* __restrict__ entries, const int32_t* __restrict__ first, int count, int m) {
+__global__ __launch_bounds__(NW* KW* kWave, OCC) void gemm_plan_kernel(const GemmPlanEntry* __restrict__ entries, int count, int m) {
     using C = Cfg<TM, TN, NW, KW, XK, CK, W, R>;
+    constexpr int size = plan_size(C::kRowsN);
     __shared__ __align__(16) uint8_t s_lds[C::LdsBytes];
     const int64_t b = blockIdx.x;
     const int blocks_m = (m + C::kRowsM - 1) / C::kRowsM;
     int lo = 0, hi = count - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;
-        if ((int64_t)first[mid] * blocks_m <= b) lo = mid;
+        if ((int64_t)entries[mid].first[size] * blocks_m <= b) lo = mid;
         else hi = mid - 1;
     }
-    const DecodeEntry& e = entries[lo];
+    const GemmPlanEntry& e = entries[lo];
     const GemmArgs a{e.packed, e.scales, e.x, e.y, e.n, e.ng, m};
-    run_tile<C, TM, TN, NW, KW, XK, CK, W, R>(a, (int)(b - (int64_t)first[lo] * blocks_m), blocks_m, (lds_u8*)s_lds);
+    run_tile<C, TM, TN, NW, KW, XK, CK, W, R>(a, (int)(b - (int64_t)e.first[size] * blocks_m), blocks_m, (lds_u8*)s_lds);
 }
 
 // ... or from the launch's own arguments (prompts: no plan to keep).
@@ -775,7 +783,7 @@ struct Config {
     int occ;  // blocks per CU
     int rows_m, rows_n;
     hipError_t (*one)(const GemmArgs&, int64_t, int, hipStream_t);
-    hipError_t (*plan)(const DecodeEntry*, const int32_t*, int, int64_t, int, hipStream_t);
+    hipError_t (*plan)(const GemmPlanEntry*, int, int64_t, int, hipStream_t);
     hipError_t (*list)(const GemmList&, int64_t, hipStream_t);
 };
 
@@ -785,11 +793,11 @@ hipError_t launch_one(const GemmArgs& a, int64_t blocks, int blocks_m, hipStream
     return hipGetLastError();
 }
 template <int TM, int TN, int NW, int KW, int XK, int CK, int W, int R, int OCC>
-hipError_t launch_plan(const DecodeEntry* entries, const int32_t* first, int count, int64_t blocks, int m, hipStream_t stream) {
+hipError_t launch_plan(const GemmPlanEntry* entries, int count, int64_t blocks, int m, hipStream_t stream) {
     if constexpr (TM <= 4) {
         using C = Cfg<TM, TN, NW, KW, XK, CK, W, R>;
-        static_assert(C::kRowsN >= 16 && C::kRowsN < 16 << kGemmPlanSizes && (C::kRowsN & (C::kRowsN - 1)) == 0, "plans hold these sizes");
-        hipLaunchKernelGGL((gemm_plan_kernel<TM, TN, NW, KW, XK, CK, W, R, OCC>), dim3((unsigned)blocks), dim3(NW * KW * kWave), 0, stream, entries, first, count, m);
+        static_assert(plan_size(C::kRowsN) < kGemmPlanSizes && C::kRowsN == 16 << plan_size(C::kRowsN), "plans hold these sizes");
+        hipLaunchKernelGGL((gemm_plan_kernel<TM, TN, NW, KW, XK, CK, W, R, OCC>), dim3((unsigned)blocks), dim3(NW * KW * kWave), 0, stream, entries, count, m);
         return hipGetLastError();
     } else {
         return hipErrorInvalidValue;  // plans are made for M <= 64 only
@@ -921,15 +929,13 @@ int gemm_plan_config(const wq_linear* lin, int count, int64_t m) {
 }
 
 int gemm_plan_size(int config) {
-    int size = 0;
-    while ((16 << size) < kConfigs[config].rows_n) ++size;
-    return size;
+    return plan_size(kConfigs[config].rows_n);
 }
 
-hipError_t launch_gemm_plan(int config, const DecodeEntry* entries, const int32_t* first, int count, int64_t blocks_n,
-                            int m, hipStream_t stream) {
+hipError_t launch_gemm_plan(int config, const GemmPlanEntry* entries, int count, int64_t blocks_n, int m,
+                            hipStream_t stream) {
     const Config& c = kConfigs[config];
-    return c.plan(entries, first, count, blocks_n * ((m + c.rows_m - 1) / c.rows_m), m, stream);
+    return c.plan(entries, count, blocks_n * ((m + c.rows_m - 1) / c.rows_m), m, stream);
 }
 
 hipError_t launch_gemm(const uint32_t* packed, const uint16_t* scales, const uint16_t* x, uint16_t* y, int64_t n,

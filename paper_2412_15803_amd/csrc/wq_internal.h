@@ -106,15 +106,26 @@ struct DecodePlan {
 
 // Small-batch decode step: independent linears in one launch of the
 // matrix-core kernel.  The block shape is picked for the whole list and the
-// number of rows m; its blocks span 16 << gemm_plan_size(config) rows of W.
-// Entry i owns the blocks from first[i] * blocks_m on, ceil(n / rows) x
-// blocks_m of them.  The plan holds `first` for every size, so that it does
-// not depend on m and one resident copy serves all batches of a list.
+// number of rows m; its blocks span 16 << size rows of W, size =
+// gemm_plan_size(config).  Entry i owns the blocks from first[size] * blocks_m
+// on, ceil(n / rows) x blocks_m of them.  The plan holds `first` for every
+// size, so that it does not depend on m and one resident copy serves all
+// batches of a list.
 constexpr int kGemmPlanSizes = 5;
+struct GemmPlanEntry {
+    const void* packed;      // [n][ng] 16-byte groups
+    const uint16_t* scales;  // [n][ng]
+    const uint16_t* x;       // [m][ng * 32]
+    uint16_t* y;             // [m][n]
+    int64_t n;
+    int32_t ng;
+    int32_t first[kGemmPlanSizes];
+};
+static_assert(sizeof(GemmPlanEntry) == 64, "GemmPlanEntry layout");
 int gemm_plan_config(const wq_linear* lin, int count, int64_t m);
 int gemm_plan_size(int config);
-hipError_t launch_gemm_plan(int config, const DecodeEntry* entries, const int32_t* first, int count, int64_t blocks_n,
-                            int m, hipStream_t stream);
+hipError_t launch_gemm_plan(int config, const GemmPlanEntry* entries, int count, int64_t blocks_n, int m,
+                            hipStream_t stream);
 
 // Small-batch decode step below kMatrixCoreMinM rows (or any small batch when
 // forced): independent linears in

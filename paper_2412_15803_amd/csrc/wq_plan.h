@@ -171,7 +171,6 @@ struct GroupPlan {
 // blocks (matrix cores) or waves (vector kernel) of the grid.
 struct BatchPlan {
     size_t off_entries;
-    size_t off_first;  // first blocks of the entries (matrix cores)
     int count;
     int64_t blocks;    // of one set of rows of x (matrix cores), or waves
     int config;        // block shape (matrix cores)

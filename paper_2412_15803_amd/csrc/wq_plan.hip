@@ -149,31 +149,31 @@ BatchPlan plan_batch_group(const wq_linear* lin, const Group& g, int64_t m, Plan
     bp.count = count;
     bp.config = gemm_plan_config(lin + g.begin, count, m);
     bp.off_entries = align16(out.size);
-    bp.off_first = align16(bp.off_entries + sizeof(DecodeEntry) * count);
-    const size_t end = align16(bp.off_first + sizeof(int32_t) * kGemmPlanSizes * count);
+    const size_t end = bp.off_entries + sizeof(GemmPlanEntry) * count;
     if (out.overflow || end > out.cap) {
         out.overflow = true;
         return bp;
     }
     std::memset(out.data + out.size, 0, end - out.size);
-    DecodeEntry* ents = reinterpret_cast<DecodeEntry*>(out.data + bp.off_entries);
-    for (int i = 0; i < count; ++i) fill_entry(ents[i], lin[g.begin + i]);
+    GemmPlanEntry* ents = reinterpret_cast<GemmPlanEntry*>(out.data + bp.off_entries);
+    for (int i = 0; i < count; ++i) {
+        const wq_linear& l = lin[g.begin + i];
+        ents[i] = GemmPlanEntry{l.packed_w, l.scales, l.x, l.y, l.N, (int32_t)(l.K / 32), {}};
+    }
     // The longest K first, so that the launch ends on short blocks (sorted
     // in place, without allocating).
-    std::sort(ents, ents + count, [](const DecodeEntry& a, const DecodeEntry& b) {
+    std::sort(ents, ents + count, [](const GemmPlanEntry& a, const GemmPlanEntry& b) {
         return a.ng != b.ng ? a.ng > b.ng : a.packed != b.packed ? a.packed < b.packed : a.y < b.y;
     });
-    int32_t* first = reinterpret_cast<int32_t*>(out.data + bp.off_first);
-    for (int size = 0; size < kGemmPlanSizes; ++size, first += count) {
+    for (int size = 0; size < kGemmPlanSizes; ++size) {
         const int64_t rows = 16 << size;
         int64_t blocks = 0;
         for (int i = 0; i < count; ++i) {
-            first[i] = (int32_t)blocks;  // a group has at most kGroupMaxRows rows
+            ents[i].first[size] = (int32_t)blocks;  // a group has at most kGroupMaxRows rows
             blocks += (ents[i].n + rows - 1) / rows;
         }
         if (size == gemm_plan_size(bp.config)) bp.blocks = blocks;
     }
-    bp.off_first += sizeof(int32_t) * gemm_plan_size(bp.config) * count;
     out.size = end;
     return bp;
 }
@@ -258,11 +258,11 @@ hipError_t launch_groups(const wq_linear* lin, const Group* groups, int ngroups,
             e = launch_grouped_m1(p, gp.max_gpl, gp.blocks, stream);
         } else {
             const BatchPlan& bp = bplans[i];
-            const DecodeEntry* ents = reinterpret_cast<const DecodeEntry*>(d_plan + bp.off_entries);
             if (matrix) {
-                const int32_t* first = reinterpret_cast<const int32_t*>(d_plan + bp.off_first);
-                e = launch_gemm_plan(bp.config, ents, first, bp.count, bp.blocks, (int)m, stream);
+                e = launch_gemm_plan(bp.config, reinterpret_cast<const GemmPlanEntry*>(d_plan + bp.off_entries), bp.count,
+                                     bp.blocks, (int)m, stream);
             } else {
+                const DecodeEntry* ents = reinterpret_cast<const DecodeEntry*>(d_plan + bp.off_entries);
                 for (int64_t m0 = 0; m0 < m && e == hipSuccess; m0 += 8)
                     e = launch_grouped_mb(ents, bp.count, bp.blocks, m0, (int)std::min<int64_t>(8, m - m0), stream);
             }
