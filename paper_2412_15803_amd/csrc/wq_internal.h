@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "wq.h"
 #include "wq_limits.h"
 
@@ -143,35 +145,72 @@ int mb_rows_for_work(int64_t work, int64_t ng);
 
 // The vector small-batch kernel walks a row's groups in 32-group tiles, two
 // row sets per wave, when those pad the row less than 64-group tiles do.
-__host__ __device__ inline bool mb_two_sets(int64_t ng) { return (ng + 31) / 32 * 32 < (ng + 63) / 64 * 64; }
-__host__ __device__ inline int64_t mb_padded_groups(int64_t ng) {
+__host__ __device__ constexpr bool mb_two_sets(int64_t ng) { return (ng + 31) / 32 * 32 < (ng + 63) / 64 * 64; }
+__host__ __device__ constexpr int64_t mb_padded_groups(int64_t ng) {
     return mb_two_sets(ng) ? (ng + 31) / 32 * 32 : (ng + 63) / 64 * 64;
+}
+
+constexpr int kMbRows = 256;  // rows of a wave of the vector kernel at most
+constexpr int kMbU = 4;       // rows of a step (per row set)
+// Waves a single small-batch linear aims for: one per SIMD (2 to 12% faster
+// than the 2048-wave split at M = 2 on the 8B-class shapes, 512 and 2048
+// slower).
+#ifndef WQ_MB_SINGLE_WAVES
+#define WQ_MB_SINGLE_WAVES (256 * 4)
+#endif
+constexpr int64_t kMbSingleWaves = WQ_MB_SINGLE_WAVES;
+
+// The vector kernel's launch of one linear.  x is loaded once per K tile and
+// wave, so the rows a wave owns set how many weight bytes each x load serves
+// (with 4 rows and 4 batch rows, x is 3.5x the weight bytes).  So: as many
+// rows per wave, in whole steps of the row's tiling (4 rows with 64-group
+// tiles, 8 with two row sets), as leave about kMbSingleWaves waves once each
+// row run's K tiles are split over up to 4 waves (two tiles each at least).
+struct MbSingle {
+    int64_t rows_per_wave, blocks;  // blocks of four waves
+    int split;
+};
+constexpr MbSingle mb_single(int64_t n, int64_t ng) {
+    const int64_t r = mb_two_sets(ng) ? 2 * kMbU : kMbU;
+    const int64_t steps = (n + r - 1) / r;
+    const int64_t ntiles = mb_two_sets(ng) ? (ng + 31) / 32 : (ng + 63) / 64;
+    int64_t max_split = 1;
+    while (max_split < 4 && ntiles >= 2 * max_split) max_split *= 2;
+    const int64_t spw = std::max<int64_t>(1, std::min<int64_t>(steps * max_split / kMbSingleWaves, kMbRows / r));
+    const int64_t rows_per_wave = spw * r;
+    const int64_t runs = (n + rows_per_wave - 1) / rows_per_wave;
+    int split = 1;
+    while (split < max_split && runs * split < kMbSingleWaves) split *= 2;
+    return MbSingle{rows_per_wave, (runs * split + 3) / 4, split};
 }
 
 // Two rows of x against one linear alone in its launch: whether the vector
 // kernel is the faster one.  The GEMM takes about one block of 16 to 128 rows
 // per CU and round, so its time steps up where N passes a power of two and
-// grows with K where N leaves CUs idle; the vector kernel's follows the bytes,
-// best where a row's 64-group tiles divide evenly over the four waves of a
-// block.  Measured at M = 2 (GEMM / vector, us, cold weights):
-//   few rows            512 x 4096 4.9 / 4.0, 2048 x 3584 5.2 / 4.7; 2560 x 4096 5.3 / 5.4, 1024 x 3072 4.9 / 5.0
-//   code rows 4 KiB apart   4096 x 8192 8.4 / 7.8, 28672 x 8192 28.6 / 27.2; 65536 x 8192 54.0 / 57.6
-//   even tiles, deep    4096 x 14336 12.2 / 11.4, 6144 x 13824 15.3 / 14.5; 8192 x 14336 16.4 / 17.5, 4096 x 10240 9.4 / 10.5
-//   N past a power of 2 20480 x 4096 15.0 / 12.8, 10240 x 14336 24.3 / 20.8; 14336 x 4096 9.8 / 10.1, 40960 x 6144 31.2 / 34.5
-//   N up to 32768       32768 x 4096 21.2 / 17.2, 28672 x 4096 16.2 / 15.7, 30720 x 14336 65.9 / 55.1; 28672 x 14336 46.4 / 48.3,
-//                       16384 x 4096 10.3 / 11.0
-// Over 357 measured shapes (N 128..128256, K 2048..16384) the choice is within 1%
-// of the faster kernel on average (always the GEMM 7.4%, always the vector
-// kernel 7.0%).
-inline bool vector_takes_pair(int64_t n, int64_t k) {
+// grows with K where N leaves CUs idle; the vector kernel's follows the bytes
+// where its blocks fill whole rounds of the CUs and a row's 64-group tiles
+// divide evenly over the waves that share it, and otherwise steps up by as
+// much as two.  Measured at M = 2 (GEMM / vector, us, cold weights):
+//   few rows              512 x 4096 5.0 / 4.2, 256 x 3328 4.8 / 4.0, 2048 x 3584 5.2 / 4.7, 2304 x 8192 8.0 / 7.3; 512 x 3072 4.9 / 5.0, 3072 x 6144 6.6 / 7.0
+//   whole rounds          10240 x 8192 16.9 / 13.6, 12288 x 16384 28.7 / 25.1, 20480 x 4096 15.7 / 13.6, 11264 x 14336 25.1 / 23.1
+//   a round nearly empty  14592 x 8192 17.3 / 23.7 (261 blocks), 25600 x 4096 16.2 / 21.5 (267), 28928 x 3584 14.8 / 22.9 (259)
+//   uneven tiles          16384 x 6144 14.5 / 17.3, 11264 x 10240 19.5 / 22.9
+//   below a power of two  16384 x 4096 10.4 / 11.5, 28672 x 4096 17.4 / 18.2, 14336 x 13312 24.9 / 28.9; 13312 x 16384 29.3 / 26.5
+//   many rows             46080 x 14336 68.6 / 82.1, 44032 x 16384 80.1 / 95.4, 128256 x 3072 39.7 / 67.9
+// Over 3500 random shapes (N 64..131072, K 1536..16384) the choice is 0.6%
+// slower than the faster kernel on average (always the GEMM 12%, always the
+// vector kernel 14%) and 12% at the 99th percentile.
+constexpr bool vector_takes_pair(int64_t n, int64_t k) {
+    if (n <= 2048) return k > 3072;
+    if (n <= 3072 && k > 6144) return true;
     const int64_t ng = k / 32, tiles = (ng + 63) / 64;
-    if (n <= 2048) return k >= 3584;
     const bool even = !mb_two_sets(ng) && (tiles == 2 || tiles % 4 == 0 || (tiles > 4 && tiles % 4 == 3));
-    if (!even || n >= 65536) return false;
-    if (k % 8192 == 0 || (tiles >= 7 && n <= 6144)) return true;
+    if (!even || n > 40960 || mb_single(n, ng).blocks % 256 != 0) return false;
+    if (tiles % 4 == 0) return true;
     int64_t half = 8192;  // the power of two below n
     while (half * 2 < n) half *= 2;
-    return n > 8192 && (n <= half + half / 4 || (n > (tiles == 2 ? 16384 : 28672) && n <= 32768));
+    if (tiles == 2) return n > 8192 && n <= half + half / 2;
+    return n <= 6144 || (n > 8192 && n <= half + half / 4);
 }
 
 // Largest groups-per-lane of the grouped kernel (K <= 16384).

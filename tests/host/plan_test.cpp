@@ -60,12 +60,13 @@ int main() {
         int64_t n, k;
         bool vector;
     } const pairs[] = {
-        {1, 3584, true},      {2048, 3584, true},    {2048, 3552, false},  {2049, 4096, false},   {512, 16384, true},
-        {2049, 8192, true},   {65535, 8192, true},   {65536, 8192, false}, {4096, 14336, true},   {6144, 13824, true},
-        {6145, 14336, false}, {4096, 10240, false},  {3072, 6144, false},  {8192, 4096, false},   {8193, 4096, true},
-        {10240, 4096, true},  {10241, 4096, false},  {16384, 4096, false}, {20480, 14336, true},  {20481, 14336, false},
-        {16385, 4096, true},  {28672, 14336, false}, {28673, 14336, true},  {32768, 4096, true},  {40960, 4096, true},   {40961, 4096, false},
-        {20480, 5120, false}, {128256, 3072, false}, {3072, 3072, false},  {16384, 3072, false},  {2560, 7168, false},
+        {1, 3104, true},      {2048, 3104, true},    {2048, 3072, false},  {2049, 4096, false},   {512, 16384, true},
+        {2049, 8192, true},   {3072, 6176, true},    {3072, 6144, false},  {3073, 8192, false},   {4096, 14336, true},
+        {6144, 14336, true},  {7168, 14336, false},  {4096, 10240, false}, {4096, 4096, false},   {8192, 4096, false},
+        {10240, 4096, true},  {10241, 4096, false},  {9216, 4096, false},  {12288, 4096, true},   {14336, 4096, false},
+        {10240, 14336, true}, {12288, 14336, false}, {14336, 8192, true},  {14592, 8192, false},  {24576, 4096, true},
+        {25600, 4096, false}, {28672, 4096, false},  {40960, 8192, true},  {41984, 8192, false},  {28928, 3584, false},
+        {20480, 5120, false}, {128256, 3072, false}, {3072, 3072, false},  {16384, 3072, false},  {3200, 7168, false},
     };
     for (const auto& p : pairs) {
         char what[96];

@@ -199,7 +199,8 @@ def test_group_sum_picked_exact(m, n, k):
 
 
 @pytest.mark.parametrize("n,k", [(1, 3584), (17, 3552), (2048, 3584), (2049, 3584), (2049, 8192), (300, 16384), (2050, 13824),
-                                 (8193, 4096), (10241, 4096)])
+                                 (8193, 4096), (10241, 4096), (17, 3072), (17, 3104), (3072, 6176), (3073, 8192),
+                                 (10240, 4096), (5120, 14336)])
 def test_two_rows_on_either_kernel_exact(n, k):
     """Both sides of the line between the vector kernel and the GEMM at
     M = 2, through wq_gemv and as the second of two dependent linears."""
