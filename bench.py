@@ -779,7 +779,7 @@ def prefill_configs(device, seed, only=None):
 
 # Counter summaries of the split kernel, by ATTN_CONFIGS index.
 ATTN_PROFILES = {0: "paged_attention_3b_ctx4096.md", 1: "paged_attention_3b_ctx32768.md"}
-ATTN_SOURCES = ("wq_attention.hip", "wq_device.h")
+ATTN_SOURCES = ("wq_attention.hip", "wq_attn_plan.h", "wq_device.h")
 
 
 def attention_traffic(index):

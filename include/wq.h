@@ -136,7 +136,7 @@ typedef struct wq_linear {
  *   M, group  shared by all linears (1 <= M <= WQ_MAX_M, group == 32).
  *
  * Library-owned resources.  For M <= 64 the call turns the list into a
- * launch plan (about 76 bytes per linear) that the kernels read from device
+ * launch plan (64 to about 76 bytes per linear) that the kernels read from device
  * memory.  Per (device, stream) pair it is called with, the library keeps,
  * until the process ends: up to 32 device plan buffers holding the plans of
  * the most recently used distinct descriptor lists, any number of frozen

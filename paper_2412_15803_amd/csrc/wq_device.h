@@ -261,11 +261,11 @@ constexpr int kRawBufferFlags = 0x00020000;  // word 3 of a raw (unswizzled) gfx
 
 // Cache policy of a buffer load: the default, or non-temporal (the lines are
 // marked as streamed and go first, so the weight stream does not push x and
-// the plan out of L2).  The whole-step kernel loads its weights
-// non-temporally: measured 4-6% faster on the 3B- and 8B-class steps.  Not
-// the single-linear kernels (the 8B down projection alone got slower), nor
-// the matrix-core kernel, whose loads read half an L2 line each and lose the
-// other half before the next item reads it.
+// the plan out of L2).  The batch-1 kernels load their weights
+// non-temporally: measured 4-6% faster on the 3B- and 8B-class steps.  So does
+// the matrix-core GEMM where it reads every weight once, in whole lines; not
+// where other blocks read the weights again from L2, nor do the vector
+// small-batch kernels, where it made no difference.
 constexpr int kCpolDefault = 0;
 constexpr int kCpolNonTemporal = 2;
 

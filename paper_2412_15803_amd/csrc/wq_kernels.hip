@@ -11,7 +11,6 @@ using namespace dev;
 
 constexpr int kBlock = 256;  // 4 waves per workgroup
 constexpr int kWavesPerBlock = kBlock / kWave;
-constexpr int kTargetWaves = 256 * 8;  // 256 CUs x 8 waves
 
 // --------------------------------------------------------------- quantize
 //
