@@ -310,7 +310,7 @@ def test_decode_matches_single_gemv_random_data():
 def test_small_batch_independent_linears_bit_exact(m):
     """Independent linears of mixed K (a group count that is not a multiple
     of 4, the 8B shapes' widths, K = 14336) and ragged N in one grouped
-    matrix-core launch per 16 batch rows; every row checked."""
+    matrix-core launch; every row checked."""
     rng = np.random.default_rng(100 + m)
     shapes = [(300, 1056), (4096, 4096), (1000, 14336), (37, 800), (6144, 4096), (257, 2080)]
     announce(f"decode small batch M={m}, {len(shapes)} independent linears")
@@ -408,7 +408,7 @@ def test_small_batch_decode_random_data_tolerance(m):
 
 @pytest.mark.parametrize("m", [3, 6, 8, 16])
 def test_small_batch_both_paths_bit_exact(m, monkeypatch):
-    """From M = 3 on the matrix cores are the default; the vector kernel
+    """The matrix cores are the default for lists; the vector kernel
     (forced through WQ_SMALL_BATCH_VECTOR, read by the library at every call)
     must give the same exact results, single GEMV and decode step alike."""
     from paper_2412_15803_amd import wq

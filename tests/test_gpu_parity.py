@@ -197,7 +197,7 @@ def test_gemv_integer_exact_small_batch(n, k, m):
 def _use_path(monkeypatch, path):
     """'vector' forces the vector small-batch kernel (the library reads
     WQ_SMALL_BATCH_VECTOR at every call); 'default' takes the library's
-    choice (the vector kernel at M = 2, the matrix cores from M = 3)."""
+    choice (the matrix cores; at M = 2 the faster of the two by its rule)."""
     if path == "vector":
         monkeypatch.setenv("WQ_SMALL_BATCH_VECTOR", "1")
     else:
@@ -287,9 +287,8 @@ def test_gemv_pow2_scales_matrix_cores_bit_exact(n, k, m):
     _gemv_case(p, s, x, None, True, "power-of-two scales")
 
 
-# Batches past 16 rows run on the matrix cores in chunks of 16 rows.  On a
-# one-tile launch with at least 32 steps of K, a last chunk of at most 8 rows
-# splits K over eight waves per block and the chunks before it over four.
+# Batches past 16 rows, in one pass over the weights: tiles of 32 to 64 rows of
+# x, K split over a block's waves where the linear has few rows.
 @pytest.mark.parametrize("n,k,m", [(300, 4096, 20), (4096, 4096, 24), (131, 14336, 40), (1000, 8192, 56)],
                          ids=lambda v: str(v))
 def test_gemv_integer_exact_matrix_core_chunks(n, k, m):
@@ -311,8 +310,8 @@ def test_gemv_integer_exact_small_batch_random_shapes(n, k, m, path, monkeypatch
 
 @pytest.mark.parametrize("m", [4, 16])
 def test_gemv_integer_exact_small_batch_3b_lm_head(m):
-    """The 3B LM head on the vector kernel (M=4) and on the matrix cores with
-    2-step chunks (M=16, the launch used for very tall linears)."""
+    """The 3B LM head, a very tall linear, on tiles of four rows of x (M=4)
+    and of sixteen (M=16)."""
     n, k = wl.LLAMA3B_LM_HEAD.n, wl.LLAMA3B_LM_HEAD.k
     p = wl.random_words_host(23, n, k)
     s = wl.constant_scales_host(n, k, 0x2400)
